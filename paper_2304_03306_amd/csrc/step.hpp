@@ -193,13 +193,34 @@ struct Geo {
   // LDS stride between transform groups that share a wavefront: TTSH_LDS_OFF
   // complex entries off a multiple of 32 (chosen by measuring LDS bank
   // conflicts on gfx950).
-  static constexpr int LS = (fft_slots(3) * NP + 31) / 32 * 32 + TTSH_LDS_OFF;
+  template <bool WAVE>
+  static constexpr int ls() {
+    return (fft_slots(3, WAVE) * NP + 31) / 32 * 32 + TTSH_LDS_OFF;
+  }
 };
 
 // index of mixed-domain entry (field f, column m, row y)
 template <int N>
 __device__ __forceinline__ size_t mix_idx(int f, int m, int y) {
   return (size_t)f * Geo<N>::MP4 * N + (size_t)(m >> 2) * (4 * N) + 4 * y + (m & 3);
+}
+
+// The same pointer, opaque to the compiler if FRESH: the factors behind it are
+// then read again instead of being kept in registers from one transform to
+// the next.  Of the sizes whose workgroups hold several wavefronts per
+// transform the largest lose more to the registers (at 8192 points they would
+// spill; at 2048 the row pass takes 160 us with the kept factors and 139 us
+// without, six paper-preset instances) than the second reads cost; up to 1024
+// points keeping them is the faster (radius sweep 69.7 against 71.5 us a step).
+constexpr int kReloadN = 2048;
+template <bool FRESH, class T>
+__device__ __forceinline__ const C2<T>* reload(const C2<T>* tw) {
+  if constexpr (FRESH) {
+    auto g = (const __attribute__((address_space(1))) C2<T>*)tw;
+    asm volatile("" : "+s"(g));
+    return (const C2<T>*)g;
+  }
+  return tw;
 }
 
 // z = p + i q
@@ -212,12 +233,6 @@ __device__ __forceinline__ C2<T> pack_pq(C2<T> p, C2<T> q) {
 // row pass: RP row pairs per workgroup, TT threads per pair; `tile` selects
 // rows 2 RP tile .. 2 RP (tile + 1) - 1 of instance `inst`
 // ---------------------------------------------------------------------------
-template <int N, int RP, class T, int SCH = kSchedDefault>
-struct RowSmem {
-  static constexpr size_t lds = (size_t)RP * Geo<N, SCH>::LS * sizeof(C2<T>);
-  static constexpr size_t bytes = lds + (size_t)(RP * Geo<N, SCH>::TT / 64) * RP * 4 * sizeof(T);
-};
-
 // The row pass's output rows in contiguous form.  For field f and slab s
 // (columns 4s..4s+3) the 2 RP rows of a tile are one run of 8 RP complex
 // values in memory (rows 2 RP tile.., four columns each).  The forcing values
@@ -239,6 +254,16 @@ struct RowStage {
   __device__ static __forceinline__ int at(int f, int m, int r) {
     return (f * S + (m >> 2)) * RS + 4 * r + (m & 3);
   }
+};
+
+template <int N, int RP, class T, int SCH = kSchedDefault>
+struct RowSmem {
+  static constexpr bool WAVE = RP * Geo<N, SCH>::TT == 64;  // one-wavefront tile
+  static constexpr int LS = Geo<N, SCH>::template ls<WAVE>();
+  static constexpr size_t runs = RowStage<N, RP, T>::bytes(2);
+  static constexpr size_t xf = (size_t)RP * LS * sizeof(C2<T>);
+  static constexpr size_t lds = xf > runs ? xf : (runs + 15) / 16 * 16;
+  static constexpr size_t bytes = lds + (size_t)(RP * Geo<N, SCH>::TT / 64) * RP * 4 * sizeof(T);
 };
 
 // the NF fields' runs of rows row0.. from LDS to memory (field stride fs,
@@ -285,7 +310,7 @@ __device__ __forceinline__ void row_body(const C2<T>* __restrict__ X, C2<T>* __r
   const C2<T>* Xp = X + inst * 3 * MP4 * N;
   C2<T>* Yp = Y + inst * NFY * MP4 * N;
   const T* Kp = K + inst * N * N;
-  C2<T>* L = lds + lane * G::LS;
+  C2<T>* L = lds + lane * RowSmem<N, RP, T, SCH>::LS;
 
   // gather Z(m) over the full row spectrum from the stored m_x = 0..M half
   C2<T> z[3][E];
@@ -348,7 +373,7 @@ __device__ __forceinline__ void row_body(const C2<T>* __restrict__ X, C2<T>* __r
     if constexpr (GW)
       wv[NFY - 1][e] = mk(-c.gamma_w * kr[0][e] * z[2][e].x, -c.gamma_w * kr[1][e] * z[2][e].y);
   }
-  fft<N, -1, NFY, SCH, NT == 64>(wv, L, t, tw);
+  fft<N, -1, NFY, SCH, NT == 64>(wv, L, t, reload<(N >= kReloadN)>(tw));
 
 #pragma unroll
   for (int r = 0; r < 2; ++r)
@@ -428,7 +453,8 @@ __device__ __forceinline__ void row_body(const C2<T>* __restrict__ X, C2<T>* __r
 // ---------------------------------------------------------------------------
 template <int N, int TC, class T, bool GW, int SCH = kSchedDefault>
 struct ColSmem {
-  static constexpr size_t fft = (size_t)TC * Geo<N, SCH>::LS * sizeof(C2<T>);
+  static constexpr int LS = Geo<N, SCH>::template ls<TC * Geo<N, SCH>::TT == 64>();
+  static constexpr size_t fft = (size_t)TC * LS * sizeof(C2<T>);
   static constexpr size_t herm = (size_t)N * sizeof(C2<double>);
   static constexpr size_t bytes = fft > herm ? fft : herm;
 };
@@ -490,7 +516,7 @@ __device__ __forceinline__ void col_body(const C2<T>* __restrict__ Y, C2<T>* __r
   const int mx = tile * TC + col;
   const bool valid = mx <= M;
   const double dk = dkv[inst];
-  C2<T>* L = reinterpret_cast<C2<T>*>(smem) + col * G::LS;
+  C2<T>* L = reinterpret_cast<C2<T>*>(smem) + col * ColSmem<N, TC, T, GW, SCH>::LS;
   constexpr int SLOTS = MODE >= 4 ? 2 : 1;                                  // kept forcing spectra
   constexpr bool STORE = !(MODE == 5 || MODE == 6);                        // the stage keeps its state
   C2<S>* stp = ((MODE == 3 || MODE == 6) ? st2 : st) + inst * 2 * MP * SP;  // state read
@@ -726,7 +752,7 @@ __device__ __forceinline__ void col_body(const C2<T>* __restrict__ Y, C2<T>* __r
     z[1][e] = cvt<T>(cscale(ny[e], sN));
     z[2][e] = cvt<T>(mk(-cw.y * dk * sN, cw.x * dk * sN));
   }
-  fft<N, +1, 3, SCH, NT == 64>(z, L, t, tw);
+  fft<N, +1, 3, SCH, NT == 64>(z, L, t, reload<(N >= kReloadN)>(tw));
   if (valid) {
     C2<T>* Xp = X + inst * 3 * G::MP4 * N;
 #pragma unroll
