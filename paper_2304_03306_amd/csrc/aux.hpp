@@ -6,8 +6,9 @@
 
 #include "common.hpp"
 #include "fft.hpp"
-#include "step.hpp"
 #include "fft_full.hpp"
+#include "readout.hpp"
+#include "step.hpp"
 
 namespace ttsh {
 
@@ -16,31 +17,12 @@ __global__ void k_pack_xy(const double* __restrict__ v, C2<double>* __restrict__
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) z[i] = mk(v[i], v[n + i]);
 }
-__global__ void k_unpack_xy(const C2<double>* __restrict__ z, double* __restrict__ v, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    v[i] = z[i].x;
-    v[n + i] = z[i].y;
-  }
-}
-__global__ void k_unpack_xy_strided(const C2<double>* __restrict__ z, float* __restrict__ v, int n,
-                                    long long stride) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    v[(long long)i * stride] = (float)z[i].x;
-    v[(long long)i * stride + 1] = (float)z[i].y;
-  }
-}
 __global__ void k_pack_xy_strided(const float* __restrict__ v, long long stride, C2<double>* __restrict__ z,
                                   int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) z[i] = mk((double)v[(long long)i * stride], (double)v[(long long)i * stride + 1]);
 }
 
-__global__ void k_real_part(const C2<double>* __restrict__ z, double* __restrict__ v, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) v[i] = z[i].x;
-}
 __global__ void k_scale_c(C2<double>* __restrict__ z, double s, size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) z[i] = cscale(z[i], s);
@@ -167,101 +149,10 @@ __global__ void k_pack_state(const C2<double>* __restrict__ Z, const C2<double>*
   st[(1 * MP + mx) * SP + pos] = cvt<S>(oy);
 }
 
-// Full spectrum of (v_x + i v_y)/N (or omega/N) from the state, ready for the
-// unnormalised inverse transform.  what = 0: velocity, 1: vorticity.
-template <class S>
-__global__ void k_state_to_full(const C2<S>* __restrict__ st, C2<double>* __restrict__ Z, int N,
-                                double dk, int what) {
-  const int M = N / 4, MP = M + 1, SP = 2 * M + 2;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N * N) return;
-  int my = mode_of(i / N, N), mx = mode_of(i % N, N);
-  C2<double> out = mk(0.0, 0.0);
-  if (mx * mx + my * my <= M * M) {
-    const bool neg = mx < 0;
-    const int ax = neg ? -mx : mx, ay = neg ? -my : my;
-    const int pos = ay >= 0 ? ay : ay + 2 * M + 1;
-    C2<double> a = cvt<double>(st[(0 * MP + ax) * SP + pos]);
-    C2<double> b = cvt<double>(st[(1 * MP + ax) * SP + pos]);
-    if (neg) {
-      a = conj(a);
-      b = conj(b);
-    }
-    if (what == 0) {
-      out = mk(a.x - b.y, a.y + b.x);  // a + i b
-    } else {
-      const C2<double> c = cscale(b, (double)mx) - cscale(a, (double)my);
-      out = mk(-c.y * dk, c.x * dk);    // i dk (m_x v_y - m_y v_x)
-    }
-    out = cscale(out, 1.0 / N);
-  }
-  Z[i] = out;
-}
-
 template <class S>
 __global__ void k_convert_c(const C2<double>* __restrict__ in, C2<S>* __restrict__ out, size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) out[i] = cvt<S>(in[i]);
-}
-
-// Batched full spectra Z of (v_x + i v_y) (unnormalised, [batch][N][N]) ->
-// Z' of the projected field: components separated, cut at m^2 > (N/4)^2,
-// Leray-projected (m != 0), recombined and scaled by 1/N^2 so that the
-// unnormalised inverse transform returns the field.
-__global__ void k_project_full(const C2<double>* __restrict__ Z, C2<double>* __restrict__ out, int N, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int b = i / (N * N), r = i % (N * N);
-  const int my = mode_of(r / N, N), mx = mode_of(r % N, N);
-  const int M = N / 4, m2 = mx * mx + my * my;
-  C2<double> o = mk(0.0, 0.0);
-  if (m2 <= M * M) {
-    const C2<double>* Zb = Z + (size_t)b * N * N;
-    const C2<double> zp = Zb[r];
-    const C2<double> zm = Zb[(size_t)((N - my) % N) * N + (N - mx) % N];
-    C2<double> ox = cscale(mk(zp.x + zm.x, zp.y - zm.y), 0.5);
-    C2<double> oy = cscale(mk(zp.y + zm.y, -(zp.x - zm.x)), 0.5);
-    if (m2 > 0) {
-      const C2<double> d = cscale(mk(mx * ox.x + my * oy.x, mx * ox.y + my * oy.y), 1.0 / m2);
-      ox = ox - cscale(d, (double)mx);
-      oy = oy - cscale(d, (double)my);
-    }
-    o = cscale(mk(ox.x - oy.y, ox.y + oy.x), 1.0 / ((double)N * N));
-  }
-  out[i] = o;
-}
-
-// Per field of a batch of projected spectra (as written by k_project_full):
-// out[2b] = sum_x |v|^2, out[2b+1] = sum_x |w|^2 with w the vorticity in
-// integer-mode units (i (m_x v_y - m_y v_x) per mode).  Block per field.
-__global__ void __launch_bounds__(256) k_full_norms(const C2<double>* __restrict__ Zs, int N,
-                                                    double* __restrict__ out) {
-  const C2<double>* Z = Zs + (size_t)blockIdx.x * N * N;
-  const double s = (double)N * N;  // undo the 1/N^2 of the stored spectrum
-  double e = 0.0, w = 0.0;
-  for (int r = threadIdx.x; r < N * N; r += blockDim.x) {
-    const int my = mode_of(r / N, N), mx = mode_of(r % N, N);
-    const C2<double> zp = cscale(Z[r], s);
-    const C2<double> zm = cscale(Z[(size_t)((N - my) % N) * N + (N - mx) % N], s);
-    const C2<double> ox = cscale(mk(zp.x + zm.x, zp.y - zm.y), 0.5);
-    const C2<double> oy = cscale(mk(zp.y + zm.y, -(zp.x - zm.x)), 0.5);
-    e += zp.x * zp.x + zp.y * zp.y;
-    const C2<double> c = cscale(oy, (double)mx) - cscale(ox, (double)my);
-    w += c.x * c.x + c.y * c.y;
-  }
-  e = wave_sum_from(e, 1);
-  w = wave_sum_from(w, 1);
-  __shared__ double red[4][2];
-  if ((threadIdx.x & 63) == 0) {
-    red[threadIdx.x >> 6][0] = e;
-    red[threadIdx.x >> 6][1] = w;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const double inv = 1.0 / ((double)N * N);  // Parseval for the unnormalised transform
-    out[2 * blockIdx.x] = (red[0][0] + red[1][0] + red[2][0] + red[3][0]) * inv;
-    out[2 * blockIdx.x + 1] = (red[0][1] + red[1][1] + red[2][1] + red[3][1]) * inv;
-  }
 }
 
 // internal state [2][M+1][2M+2]  <->  interface layout [2][2M+1][M+1] (FP64)
@@ -311,63 +202,45 @@ __global__ void k_resample(const C2<S>* __restrict__ src, int Ns, C2<double>* __
   dst[i] = v;
 }
 
-// ---- order parameters on the real-space fields ------------------------------
-// Vortex order parameter about (cx, cy) of the velocity in Z (real part v_x,
-// imaginary part v_y, node (i, j) at x = (j - N/2) dx, y = (i - N/2) dx):
-// sums of |e_theta . v| and |v| in FP64 in a fixed order.
-//
-// The reductions over the N^2 nodes here run in order_blocks(N) workgroups of
-// 1024 threads, each writing one partial result; a one-thread kernel combines
-// the partials in workgroup order, so that results do not vary between runs.
+// ---- order parameters and defects of the real-space fields --------------------
+// Combines the row kernel's partials (kOrderPart values per workgroup: sums of
+// |e_theta . v| and |v|, and per region the largest |omega| with its node and
+// value) into out[0] = Psi (paper's normalisation) and out[1] = Psi_2 =
+// |w_l + w_r| / (|w_l| + |w_r|), NaN for an empty region.  Thread t takes the
+// workgroups t, t + 256, ... in order and the threads are combined by a tree,
+// so that results do not vary between runs.
+__global__ void __launch_bounds__(256) k_order_final(const double* __restrict__ part, int nb,
+                                                     double* __restrict__ out) {
+  __shared__ double red[256][kOrderPart];
+  const int t = threadIdx.x;
+  double* a = red[t];
+  for (int q = 0; q < kOrderPart; ++q) a[q] = 0.0;
+  a[2] = a[5] = -1.0;
+  auto add = [&](const double* p) {
+    a[0] += p[0];
+    a[1] += p[1];
+    for (int s = 2; s < kOrderPart; s += 3) order_best(a[s], a[s + 1], a[s + 2], p[s], p[s + 1], p[s + 2]);
+  };
+  for (int q = t; q < nb; q += 256) add(part + (size_t)q * kOrderPart);
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if (t < o) add(red[t + o]);
+    __syncthreads();
+  }
+  if (t == 0) {
+    const double two_pi = 2.0 / M_PI;
+    out[0] = (a[0] / a[1] - two_pi) / (1.0 - two_pi);
+    const double wl = a[4], wr = a[7];
+    out[1] = (a[2] < 0.0 || a[5] < 0.0) ? __builtin_nan("") : fabs(wl + wr) / (fabs(wl) + fabs(wr));
+  }
+}
+
+// The counts over the N^2 nodes run in order_blocks(N) workgroups of 1024
+// threads, each writing one partial result.
+constexpr int kOrderMaxBlocks = 256;
 inline int order_blocks(int N) {
   const int b = N * N / 4096;
-  return b < 1 ? 1 : (b > 256 ? 256 : b);  // at most kOrderMaxBlocks
-}
-__global__ void __launch_bounds__(1024) k_order_psi(const C2<double>* __restrict__ Z, int N, double dx, double cx,
-                                                    double cy, double* __restrict__ part) {
-  double num = 0.0, den = 0.0;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < N * N; i += gridDim.x * blockDim.x) {
-    const double x = ((i % N) - N / 2) * dx - cx, y = ((i / N) - N / 2) * dx - cy;
-    const double r = sqrt(x * x + y * y);
-    const C2<double> v = Z[i];
-    if (r > 0.0) num += fabs((-y * v.x + x * v.y) / r);
-    den += sqrt(v.x * v.x + v.y * v.y);
-  }
-  num = wave_sum_from(num, 1);
-  den = wave_sum_from(den, 1);
-  __shared__ double red[16][2];
-  if ((threadIdx.x & 63) == 0) {
-    red[threadIdx.x >> 6][0] = num;
-    red[threadIdx.x >> 6][1] = den;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double a = 0.0, b = 0.0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
-      a += red[w][0];
-      b += red[w][1];
-    }
-    part[2 * blockIdx.x] = a;
-    part[2 * blockIdx.x + 1] = b;
-  }
-}
-// The combining kernels run one workgroup of 256 threads: the partials
-// (at most 256 per quantity) are staged in LDS in parallel, then one thread
-// takes them in workgroup order.
-constexpr int kOrderMaxBlocks = 256;
-__global__ void __launch_bounds__(256) k_order_psi_final(const double* __restrict__ part, int nb,
-                                                         double* __restrict__ out) {
-  __shared__ double ps[2 * kOrderMaxBlocks];
-  for (int q = threadIdx.x; q < 2 * nb; q += blockDim.x) ps[q] = part[q];
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  double a = 0.0, b = 0.0;
-  for (int q = 0; q < nb; ++q) {
-    a += ps[2 * q];
-    b += ps[2 * q + 1];
-  }
-  const double two_pi = 2.0 / M_PI;
-  out[0] = (a / b - two_pi) / (1.0 - two_pi);
+  return b < 1 ? 1 : (b > kOrderMaxBlocks ? kOrderMaxBlocks : b);
 }
 
 // Topological defects of the direction field of v = (Re Z, Im Z).  A node is
@@ -475,92 +348,6 @@ __global__ void __launch_bounds__(256) k_vortex_final(const int* __restrict__ pa
   }
   out[0] = a;
   out[1] = b;
-}
-
-// Two-chamber order parameter from the vorticity in the real part of Z: the
-// nodes of largest |omega| in the left and right regions (ties to the lower
-// index), |w_l + w_r| / (|w_l| + |w_r|).  Regions: with D > 0 the nodes within
-// D/2 of (cx - D/2, cy) left of x = cx and within D/2 of (cx + D/2, cy) at or
-// right of it; with D <= 0 the two half-planes.  An empty region gives NaN.
-// The disk test rounds every product and sum separately (no fused
-// multiply-add), so that a node on a disk's rim falls on the same side as in
-// a plain evaluation of the same expression.
-__global__ void __launch_bounds__(1024) k_order_psi2(const C2<double>* __restrict__ Z, int N, double dx, double cx,
-                                                     double cy, double D, double* __restrict__ part) {
-  const double r2 = __dmul_rn(0.5 * D, 0.5 * D);
-  const double cl = __dsub_rn(cx, 0.5 * D), cr = __dadd_rn(cx, 0.5 * D);
-  double best[2] = {-1.0, -1.0};
-  int at[2] = {0, 0};
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < N * N; i += gridDim.x * blockDim.x) {
-    const double x = __dmul_rn((double)((i % N) - N / 2), dx);
-    const int side = x < cx ? 0 : 1;
-    if (D > 0.0) {
-      const double y = __dmul_rn((double)((i / N) - N / 2), dx);
-      const double ex = __dsub_rn(x, side ? cr : cl), ey = __dsub_rn(y, cy);
-      if (__dadd_rn(__dmul_rn(ex, ex), __dmul_rn(ey, ey)) > r2) continue;
-    }
-    const double a = fabs(Z[i].x);
-    if (a > best[side]) {  // i grows per thread: the first of equal values is kept
-      best[side] = a;
-      at[side] = i;
-    }
-  }
-  __shared__ double bv[2][1024];
-  __shared__ int bi[2][1024];
-  for (int q = 0; q < 2; ++q) {
-    bv[q][threadIdx.x] = best[q];
-    bi[q][threadIdx.x] = at[q];
-  }
-  __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) {
-      for (int q = 0; q < 2; ++q) {
-        const double v2 = bv[q][threadIdx.x + o];
-        const int i2 = bi[q][threadIdx.x + o];
-        if (v2 > bv[q][threadIdx.x] || (v2 == bv[q][threadIdx.x] && i2 < bi[q][threadIdx.x])) {
-          bv[q][threadIdx.x] = v2;
-          bi[q][threadIdx.x] = i2;
-        }
-      }
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {  // (best |w|, its node) per side; node indices < 2^53 are exact
-    part[4 * blockIdx.x] = bv[0][0];
-    part[4 * blockIdx.x + 1] = (double)bi[0][0];
-    part[4 * blockIdx.x + 2] = bv[1][0];
-    part[4 * blockIdx.x + 3] = (double)bi[1][0];
-  }
-}
-// larger |w| wins, equal values go to the lower node: the same choice in any
-// order, so the partials are combined by a tree in LDS
-__global__ void __launch_bounds__(256) k_order_psi2_final(const C2<double>* __restrict__ Z,
-                                                          const double* __restrict__ part, int nb,
-                                                          double* __restrict__ out) {
-  __shared__ double bv[2][kOrderMaxBlocks];
-  __shared__ long long bi[2][kOrderMaxBlocks];
-  const int t = threadIdx.x;
-  for (int sd = 0; sd < 2; ++sd) {
-    bv[sd][t] = t < nb ? part[4 * t + 2 * sd] : -1.0;
-    bi[sd][t] = t < nb ? (long long)part[4 * t + 2 * sd + 1] : 0;
-  }
-  __syncthreads();
-  for (int o = kOrderMaxBlocks / 2; o > 0; o >>= 1) {
-    if (t < o)
-      for (int sd = 0; sd < 2; ++sd) {
-        const double v = bv[sd][t + o];
-        const long long i = bi[sd][t + o];
-        if (v > bv[sd][t] || (v == bv[sd][t] && v >= 0.0 && i < bi[sd][t])) {
-          bv[sd][t] = v;
-          bi[sd][t] = i;
-        }
-      }
-    __syncthreads();
-  }
-  if (t == 0) {
-    const double wl = Z[bi[0][0]].x, wr = Z[bi[1][0]].x;
-    out[1] = (bv[0][0] < 0.0 || bv[1][0] < 0.0) ? __builtin_nan("") : fabs(wl + wr) / (fabs(wl) + fabs(wr));
-  }
 }
 
 // ---- Lyapunov re-orthonormalisation -------------------------------------------

@@ -8,12 +8,22 @@
 namespace ttsh {
 
 struct MultiArgs;
+struct RowsOut;
 
-// Full-array transforms compiled per grid size (set-up and read-out paths).
+// Transforms outside the time loop, compiled per grid size.
 struct SizeOps {
   // unnormalised 2D transform of `batch` N x N complex arrays in place;
   // dir = -1 forward, +1 inverse; fp64 selects double (else float) data
   hipError_t (*fft2)(void* a, int batch, int dir, int fp64, const void* tw, hipStream_t);
+  // fields from spectra and the projection of fields (readout.hpp); tw: the
+  // FP64 factors of this size
+  hipError_t (*synth_cols)(const void* st, int st_fp64, int Ns, int Mk, double dk, int comp, void* G, const void* tw,
+                           hipStream_t);
+  hipError_t (*synth_rows)(const RowsOut&, hipStream_t);
+  hipError_t (*project_rows)(const float* v, long long stride, int batch, void* G, const void* tw, hipStream_t);
+  hipError_t (*project_cols)(void* G, int batch, double* part, const void* tw, hipStream_t);
+  int row_groups;  // workgroups of synth_rows per field
+  int col_groups;  // workgroups of project_cols per field
 };
 
 // Time-step passes over every size class of a context, compiled per

@@ -17,6 +17,7 @@
 #include "../../include/ttsh.h"
 #include "aux.hpp"
 #include "launch.hpp"
+#include "readout.hpp"
 #include "step_multi.hpp"
 
 using namespace ttsh;
@@ -212,11 +213,10 @@ struct ttsh_ctx {
   double* dnorm = nullptr;               // [n_inst][5]; kNormBlocks x 5 partials follow
   int* dflags = nullptr;                 // [n_inst] non-finite flags of the guard
   int guard_every = 50;                  // steps between guard checks inside ttsh_step (0: only at ttsh_sync)
-  void* pb0 = nullptr;                   // batched coarse-field spectra (grown on demand)
-  void* pb1 = nullptr;
-  size_t pb_cap = 0;                     // bytes of each
+  void* pb = nullptr;                    // batched coarse-field columns (grown on demand)
+  size_t pb_cap = 0;                     // its bytes
   double* pnorm = nullptr;               // [pnorm_cap][2]
-  int pnorm_cap = 0;
+  size_t pnorm_cap = 0;
   void* lyq = nullptr;                   // Lyapunov vectors: kMaxLyap logs, then [p][state] FP64
   size_t lyq_cap = 0;                    // bytes
   double* psdf = nullptr;                // PSD frequencies [kMaxPsdFreqs], then S [kMaxPsdFreqs]
@@ -591,6 +591,30 @@ int twiddles64(ttsh_ctx* c, int N, const void** out) {
   return TTSH_OK;
 }
 
+// The columns of an instance's fields on an N grid, transformed along y into
+// G ((N/4+1) x N entries of the components of `comp`, at most 12 N^2 + 48 N
+// bytes); N may differ from the instance's own grid.
+int spectrum_columns(ttsh_ctx* c, int inst, int N, int comp, void* G) {
+  auto [ci, j] = c->loc[inst];
+  SizeClass& k = c->cls[ci];
+  const void* tw = nullptr;
+  if (int rc = twiddles64(c, N, &tw)) return rc;
+  HIPCHK(size_ops(N)->synth_cols(at<const char>(k.st, k.sSt(), elem_state(c->prec), j), c->prec != 32, k.N,
+                                 std::min(N, k.N) / 4, 2.0 * M_PI / c->L[inst], comp, G, tw, c->stream));
+  return TTSH_OK;
+}
+
+// the row kernel's arguments for those columns (all of the N grid's)
+RowsOut rows_of(ttsh_ctx* c, int N, int comp, const void* G) {
+  RowsOut a{};
+  a.G = (const C2<double>*)G;
+  a.tw = (const C2<double>*)c->tw64[N];
+  a.batch = 1;
+  a.Mk = N / 4;
+  a.comp = comp;
+  return a;
+}
+
 // forward FP64 FFT of a real field pair v [2][N][N] (device) into scr0
 int field_to_spectrum(ttsh_ctx* c, int N, const double* v) {
   const int n = N * N;
@@ -805,7 +829,7 @@ void free_ctx(ttsh_ctx* c) {
   if (c->scr1) hipFree(c->scr1);
   if (c->dnorm) hipFree(c->dnorm);
   if (c->dflags) hipFree(c->dflags);
-  for (void* p : {c->pb0, c->pb1, (void*)c->pnorm, c->lyq, (void*)c->psdf})
+  for (void* p : {c->pb, (void*)c->pnorm, c->lyq, (void*)c->psdf})
     if (p) hipFree(p);
   if (c->cap) hipStreamDestroy(c->cap);
   for (int g = 0; g < kMaxGroups; ++g) {
@@ -1103,26 +1127,16 @@ int ttsh_get_field(ttsh_ctx* c, int inst, double* v, double* omega, int where) {
   int rc = check_inst(c, inst);
   if (rc) return rc;
   if (!v) return fail(TTSH_EINVAL, "null output");
-  auto [ci, j] = c->loc[inst];
-  SizeClass& k = c->cls[ci];
-  const int N = k.N, n = N * N;
-  const double dk = 2.0 * M_PI / c->L[inst];
+  const int N = c->N[inst], n = N * N;
   for (int what = 0; what < (omega ? 2 : 1); ++what) {
-    if (c->prec == 32)
-      hipLaunchKernelGGL(k_state_to_full<float>, dim3(nblk(n)), dim3(kB), 0, c->stream,
-                         at<const C2<float>>(k.st, k.sSt(), sizeof(C2<float>), j), (C2<double>*)c->scr0, N, dk, what);
-    else
-      hipLaunchKernelGGL(k_state_to_full<double>, dim3(nblk(n)), dim3(kB), 0, c->stream,
-                         at<const C2<double>>(k.st, k.sSt(), sizeof(C2<double>), j), (C2<double>*)c->scr0, N, dk, what);
-    HIPCHK(hipGetLastError());
-    HIPCHK(size_ops(N)->fft2(c->scr0, 1, +1, 1, c->tw64[N], c->stream));
     double* out = what == 0 ? v : omega;
     double* dst = where == TTSH_DEVICE ? out : (double*)c->scr1;
-    if (what == 0)
-      hipLaunchKernelGGL(k_unpack_xy, dim3(nblk(n)), dim3(kB), 0, c->stream, (const C2<double>*)c->scr0, dst, n);
-    else
-      hipLaunchKernelGGL(k_real_part, dim3(nblk(n)), dim3(kB), 0, c->stream, (const C2<double>*)c->scr0, dst, n);
-    HIPCHK(hipGetLastError());
+    const int comp = what == 0 ? kCompV : kCompW;
+    if ((rc = spectrum_columns(c, inst, N, comp, c->scr0))) return rc;
+    RowsOut a = rows_of(c, N, comp, c->scr0);
+    a.kind = what == 0 ? kOutPlanar : kOutReal;
+    a.out = dst;
+    HIPCHK(size_ops(N)->synth_rows(a, c->stream));
     if (where != TTSH_DEVICE)
       HIPCHK(hipMemcpyAsync(out, dst, sizeof(double) * (what == 0 ? 2 : 1) * n, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
@@ -1137,28 +1151,14 @@ int ttsh_get_field_coarse(ttsh_ctx* c, int inst, int Nc, float* out, int64_t pix
   if (pix_stride < 2) return fail(TTSH_EINVAL, "pix_stride must be >= 2");
   if (!size_ops(Nc)) return fail(TTSH_EUNSUPPORTED, "Nc must be one of 64, 128, 256, 512, 1024, 2048, 4096, 8192");
   if (Nc > max_N(c)) return fail(TTSH_EINVAL, "Nc larger than the context's largest grid");
-  auto [ci, j] = c->loc[inst];
-  SizeClass& k = c->cls[ci];
-  const int N = k.N, n = Nc * Nc;
-  // compact FP64 spectrum at Nc in scr1, full spectrum in scr0 (both hold
-  // max_N^2 complex values, enough for Nc <= max_N)
-  const size_t ncomp = (size_t)2 * (Nc / 4 + 1) * (Nc / 2 + 2);
-  C2<double>* comp = (C2<double>*)c->scr1;
-  if (c->prec == 32)
-    hipLaunchKernelGGL(k_resample<float>, dim3(nblk(ncomp)), dim3(kB), 0, c->stream,
-                       at<const C2<float>>(k.st, k.sSt(), sizeof(C2<float>), j), N, comp, Nc);
-  else
-    hipLaunchKernelGGL(k_resample<double>, dim3(nblk(ncomp)), dim3(kB), 0, c->stream,
-                       at<const C2<double>>(k.st, k.sSt(), sizeof(C2<double>), j), N, comp, Nc);
-  hipLaunchKernelGGL(k_state_to_full<double>, dim3(nblk(n)), dim3(kB), 0, c->stream, comp,
-                     (C2<double>*)c->scr0, Nc, 2.0 * M_PI / c->L[inst], 0);
-  HIPCHK(hipGetLastError());
-  const void* tw = nullptr;
-  if ((rc = twiddles64(c, Nc, &tw))) return rc;
-  HIPCHK(size_ops(Nc)->fft2(c->scr0, 1, +1, 1, tw, c->stream));
-  hipLaunchKernelGGL(k_unpack_xy_strided, dim3(nblk(n)), dim3(kB), 0, c->stream, (const C2<double>*)c->scr0,
-                     out, n, (long long)pix_stride);
-  HIPCHK(hipGetLastError());
+  if ((rc = spectrum_columns(c, inst, Nc, kCompV, c->scr0))) return rc;
+  RowsOut a = rows_of(c, Nc, kCompV, c->scr0);
+  a.Mk = std::min(Nc, c->N[inst]) / 4;
+  a.kind = kOutFloat;
+  a.out = out;
+  a.stride = pix_stride;
+  a.vec = pix_stride % 2 == 0 && ((uintptr_t)out & 7) == 0;
+  HIPCHK(size_ops(Nc)->synth_rows(a, c->stream));
   return TTSH_OK;
 }
 
@@ -1204,48 +1204,53 @@ int ttsh_project_coarse(ttsh_ctx* c, int N, float* v, int64_t pix_stride, int ba
   if (!size_ops(N)) return fail(TTSH_EUNSUPPORTED, "N must be one of 64, 128, 256, 512, 1024, 2048, 4096, 8192");
   const size_t n = (size_t)batch * N * N;
   if (n > (size_t)INT32_MAX) return fail(TTSH_EINVAL, "batch too large");
-  const size_t bytes = n * sizeof(C2<double>);
+  const SizeOps* ops = size_ops(N);
+  const size_t bytes = (size_t)batch * (N / 4 + 1) * N * 2 * sizeof(C2<double>);
   if (bytes > c->pb_cap) {
-    for (void** p : {&c->pb0, &c->pb1})
-      if (*p) {
-        hipFree(*p);
-        *p = nullptr;
-      }
+    if (c->pb) hipFree(c->pb);
+    c->pb = nullptr;
     c->pb_cap = 0;
-    if (hipMalloc(&c->pb0, bytes) != hipSuccess || hipMalloc(&c->pb1, bytes) != hipSuccess)
-      return fail(TTSH_ENOMEM, "projection buffers");
+    if (hipMalloc(&c->pb, bytes) != hipSuccess) return fail(TTSH_ENOMEM, "projection buffers");
     c->pb_cap = bytes;
   }
-  if (norms && batch > c->pnorm_cap) {
+  const size_t parts = (size_t)batch * ops->col_groups;
+  if (norms && parts > c->pnorm_cap) {
     if (c->pnorm) hipFree(c->pnorm);
     c->pnorm = nullptr;
     c->pnorm_cap = 0;
-    if (hipMalloc((void**)&c->pnorm, sizeof(double) * 2 * batch) != hipSuccess)
+    if (hipMalloc((void**)&c->pnorm, sizeof(double) * 2 * parts) != hipSuccess)
       return fail(TTSH_ENOMEM, "norm buffer");
-    c->pnorm_cap = batch;
+    c->pnorm_cap = parts;
   }
   int rc;
   const void* tw = nullptr;
   if ((rc = twiddles64(c, N, &tw))) return rc;
-  hipLaunchKernelGGL(k_pack_xy_strided, dim3(nblk(n)), dim3(kB), 0, c->stream, (const float*)v,
-                     (long long)pix_stride, (C2<double>*)c->pb0, (int)n);
-  HIPCHK(hipGetLastError());
-  HIPCHK(size_ops(N)->fft2(c->pb0, batch, -1, 1, tw, c->stream));
-  hipLaunchKernelGGL(k_project_full, dim3(nblk(n)), dim3(kB), 0, c->stream, (const C2<double>*)c->pb0,
-                     (C2<double>*)c->pb1, N, (int)n);
-  HIPCHK(hipGetLastError());
+  HIPCHK(ops->project_rows(v, (long long)pix_stride, batch, c->pb, tw, c->stream));
+  HIPCHK(ops->project_cols(c->pb, batch, norms ? c->pnorm : nullptr, tw, c->stream));
+  RowsOut a{};
+  a.G = (const C2<double>*)c->pb;
+  a.tw = (const C2<double>*)tw;
+  a.batch = batch;
+  a.Mk = N / 4;
+  a.comp = kCompV;
+  a.kind = kOutFloat;
+  a.out = v;
+  a.stride = pix_stride;
+  a.vec = pix_stride % 2 == 0 && ((uintptr_t)v & 7) == 0;
+  HIPCHK(ops->synth_rows(a, c->stream));
   if (norms) {
-    hipLaunchKernelGGL(k_full_norms, dim3(batch), dim3(256), 0, c->stream, (const C2<double>*)c->pb1, N,
-                       c->pnorm);
-    HIPCHK(hipGetLastError());
-  }
-  HIPCHK(size_ops(N)->fft2(c->pb1, batch, +1, 1, tw, c->stream));
-  hipLaunchKernelGGL(k_unpack_xy_strided, dim3(nblk(n)), dim3(kB), 0, c->stream, (const C2<double>*)c->pb1, v,
-                     (int)n, (long long)pix_stride);
-  HIPCHK(hipGetLastError());
-  if (norms) {
-    HIPCHK(hipMemcpyAsync(norms, c->pnorm, sizeof(double) * 2 * batch, hipMemcpyDeviceToHost, c->stream));
+    std::vector<double> h(2 * parts);
+    HIPCHK(hipMemcpyAsync(h.data(), c->pnorm, sizeof(double) * h.size(), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
+    for (int b = 0; b < batch; ++b) {
+      double e = 0.0, w = 0.0;
+      for (int g = 0; g < ops->col_groups; ++g) {
+        e += h[2 * ((size_t)b * ops->col_groups + g)];
+        w += h[2 * ((size_t)b * ops->col_groups + g) + 1];
+      }
+      norms[2 * b] = e;
+      norms[2 * b + 1] = w;
+    }
   }
   return TTSH_OK;
 }
@@ -1254,34 +1259,20 @@ int ttsh_project_coarse(ttsh_ctx* c, int N, float* v, int64_t pix_stride, int ba
 // from the vorticity), the first from_what of them skipped; the host receives
 // dnorm[from_what..1] in out[0..].
 static int order_impl(ttsh_ctx* c, int inst, double cx, double cy, double D, int from_what, double* out) {
-  auto [ci, j] = c->loc[inst];
-  SizeClass& k = c->cls[ci];
-  const int N = k.N, n = N * N;
-  const double L = c->L[inst], dk = 2.0 * M_PI / L, dx = L / N;
-  for (int what = from_what; what < 2; ++what) {
-    if (c->prec == 32)
-      hipLaunchKernelGGL(k_state_to_full<float>, dim3(nblk(n)), dim3(kB), 0, c->stream,
-                         at<const C2<float>>(k.st, k.sSt(), sizeof(C2<float>), j), (C2<double>*)c->scr0, N, dk, what);
-    else
-      hipLaunchKernelGGL(k_state_to_full<double>, dim3(nblk(n)), dim3(kB), 0, c->stream,
-                         at<const C2<double>>(k.st, k.sSt(), sizeof(C2<double>), j), (C2<double>*)c->scr0, N, dk, what);
-    HIPCHK(hipGetLastError());
-    HIPCHK(size_ops(N)->fft2(c->scr0, 1, +1, 1, c->tw64[N], c->stream));
-    // partials in scr1 (free here; at least 64^2 complex doubles, 4 per workgroup needed)
-    const int nb = order_blocks(N);
-    double* part = (double*)c->scr1;
-    if (what == 0) {
-      hipLaunchKernelGGL(k_order_psi, dim3(nb), dim3(1024), 0, c->stream, (const C2<double>*)c->scr0, N, dx, cx, cy,
-                         part);
-      hipLaunchKernelGGL(k_order_psi_final, dim3(1), dim3(256), 0, c->stream, (const double*)part, nb, c->dnorm);
-    } else {
-      hipLaunchKernelGGL(k_order_psi2, dim3(nb), dim3(1024), 0, c->stream, (const C2<double>*)c->scr0, N, dx, cx,
-                         cy, D, part);
-      hipLaunchKernelGGL(k_order_psi2_final, dim3(1), dim3(256), 0, c->stream, (const C2<double>*)c->scr0,
-                         (const double*)part, nb, c->dnorm);
-    }
-    HIPCHK(hipGetLastError());
-  }
+  const int N = c->N[inst], comp = from_what == 0 ? kCompVW : kCompW;
+  int rc;
+  if ((rc = spectrum_columns(c, inst, N, comp, c->scr0))) return rc;
+  RowsOut a = rows_of(c, N, comp, c->scr0);
+  a.kind = kOutOrder;
+  a.dx = c->L[inst] / N;
+  a.cx = cx;
+  a.cy = cy;
+  a.D = D;
+  a.out = c->scr1;  // partials, kOrderPart values per workgroup
+  HIPCHK(size_ops(N)->synth_rows(a, c->stream));
+  hipLaunchKernelGGL(k_order_final, dim3(1), dim3(256), 0, c->stream, (const double*)c->scr1, size_ops(N)->row_groups,
+                     c->dnorm);
+  HIPCHK(hipGetLastError());
   HIPCHK(hipMemcpyAsync(out, c->dnorm + from_what, (2 - from_what) * sizeof(double), hipMemcpyDeviceToHost,
                         c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
@@ -1431,19 +1422,15 @@ int ttsh_vortices(ttsh_ctx* c, int inst, double kmax, double vmin, int* out) {
   if (!(vmin >= 0.0)) return fail(TTSH_EINVAL, "vmin must be >= 0");
   auto [ci, j] = c->loc[inst];
   SizeClass& k = c->cls[ci];
-  const int N = k.N, n = N * N;
-  const double dk = 2.0 * M_PI / c->L[inst];
-  if (c->prec == 32)
-    hipLaunchKernelGGL(k_state_to_full<float>, dim3(nblk(n)), dim3(kB), 0, c->stream,
-                       at<const C2<float>>(k.st, k.sSt(), sizeof(C2<float>), j), (C2<double>*)c->scr0, N, dk, 0);
-  else
-    hipLaunchKernelGGL(k_state_to_full<double>, dim3(nblk(n)), dim3(kB), 0, c->stream,
-                       at<const C2<double>>(k.st, k.sSt(), sizeof(C2<double>), j), (C2<double>*)c->scr0, N, dk, 0);
-  HIPCHK(hipGetLastError());
-  HIPCHK(size_ops(N)->fft2(c->scr0, 1, +1, 1, c->tw64[N], c->stream));
+  const int N = k.N;
+  if ((rc = spectrum_columns(c, inst, N, kCompV, c->scr1))) return rc;
+  RowsOut a = rows_of(c, N, kCompV, c->scr1);
+  a.kind = kOutComplex;
+  a.out = c->scr0;
+  HIPCHK(size_ops(N)->synth_rows(a, c->stream));
   int* dcount = reinterpret_cast<int*>(c->dnorm);  // [2], inside the norms scratch
   const int nb = order_blocks(N);
-  int* part = (int*)c->scr1;  // per-workgroup partials (scr1 is free here)
+  int* part = (int*)c->scr1;  // per-workgroup partials (scr1 is free again)
   if (c->prec == 64)
     hipLaunchKernelGGL(k_vortex_count<double>, dim3(nb), dim3(1024), 0, c->stream, (const C2<double>*)c->scr0,
                        at<const double>(k.K, k.sK(), sizeof(double), j), N, kmax, vmin, part);
