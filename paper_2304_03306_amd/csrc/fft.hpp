@@ -152,30 +152,48 @@ __device__ __forceinline__ void bfly(C2<T>& a, C2<T>& b, T c, T s) {  // w = c +
   b = mk(fma((T)2, a.x, -x), fma((T)2, a.y, -y));
   a = mk(x, y);
 }
-// the factor w; tables hold the forward sign
 template <int DIR, class T>
-__device__ __forceinline__ C2<T> factor(const C2<T>* __restrict__ tw, int j) {
-  const C2<T> w = tw[j];
+__device__ __forceinline__ C2<T> turn(C2<T> w) {  // tables hold the forward sign
   return DIR > 0 ? conj(w) : w;
 }
 
+// The four factors a thread's butterflies of one stage take: those of its one
+// radix-8 butterfly, of its two radix-4 or of its four radix-2 ones.
+template <int N, int R, int P, class T>
+__device__ __forceinline__ void load_factors(C2<T> (&w)[4], const C2<T>* __restrict__ tw, int t) {
+  constexpr int TT = N / kFftE, NB = kFftE / R;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int j = ((t + b * TT) & (P - 1)) * (N / (P * R));
+    if constexpr (R == 8) {
+      w[0] = tw[4 * j];
+      w[1] = tw[2 * j];
+      w[2] = tw[j];
+      w[3] = tw[j + N / 8];
+    } else if constexpr (R == 4) {
+      w[2 * b] = tw[2 * j];
+      w[2 * b + 1] = tw[j];
+    } else {
+      w[b] = tw[j];
+    }
+  }
+}
+
 template <int R, int DIR, class T>
-struct DftTw;
+struct DftTw;  // run(u, factors, butterfly)
 
 template <int DIR, class T>
 struct DftTw<2, DIR, T> {
-  template <int N>
-  __device__ static __forceinline__ void run(C2<T> (&u)[2], const C2<T>* __restrict__ tw, int j) {
-    const C2<T> w = factor<DIR>(tw, j);
+  __device__ static __forceinline__ void run(C2<T> (&u)[2], const C2<T> (&f)[4], int b) {
+    const C2<T> w = turn<DIR>(f[b]);
     bfly(u[0], u[1], w.x, w.y);
   }
 };
 
 template <int DIR, class T>
 struct DftTw<4, DIR, T> {
-  template <int N>
-  __device__ static __forceinline__ void run(C2<T> (&u)[4], const C2<T>* __restrict__ tw, int j) {
-    const C2<T> w2 = factor<DIR>(tw, 2 * j), w = factor<DIR>(tw, j);
+  __device__ static __forceinline__ void run(C2<T> (&u)[4], const C2<T> (&f)[4], int b) {
+    const C2<T> w2 = turn<DIR>(f[2 * b]), w = turn<DIR>(f[2 * b + 1]);
     bfly(u[0], u[2], w2.x, w2.y);  // even q, odd q
     bfly(u[1], u[3], w2.x, w2.y);
     bfly(u[0], u[1], w.x, w.y);                // q = 0, 2
@@ -188,10 +206,8 @@ struct DftTw<4, DIR, T> {
 
 template <int DIR, class T>
 struct DftTw<8, DIR, T> {
-  template <int N>
-  __device__ static __forceinline__ void run(C2<T> (&u)[8], const C2<T>* __restrict__ tw, int j) {
-    const C2<T> w4 = factor<DIR>(tw, 4 * j), w2 = factor<DIR>(tw, 2 * j);
-    const C2<T> w = factor<DIR>(tw, j), w1 = factor<DIR>(tw, j + N / 8);
+  __device__ static __forceinline__ void run(C2<T> (&u)[8], const C2<T> (&f)[4], int) {
+    const C2<T> w4 = turn<DIR>(f[0]), w2 = turn<DIR>(f[1]), w = turn<DIR>(f[2]), w1 = turn<DIR>(f[3]);
 #pragma unroll
     for (int a = 0; a < 4; ++a) bfly(u[a], u[a + 4], w4.x, w4.y);  // even q in 0..3, odd in 4..7
 #pragma unroll
@@ -203,12 +219,41 @@ struct DftTw<8, DIR, T> {
     bfly(u[2], u[3], -DIR * w.y, DIR * w.x);   // q = 2, 6
     bfly(u[4], u[5], w1.x, w1.y);              // q = 1, 5
     bfly(u[6], u[7], -DIR * w1.y, DIR * w1.x);  // q = 3, 7
-    const C2<T> x1 = u[1], x3 = u[3], x5 = u[5], x6 = u[6];
+    const C2<T> x1 = u[1], x3 = u[3], x6 = u[6];
     u[1] = u[4];
     u[4] = x1;
     u[3] = x6;
     u[6] = x3;
-    u[5] = x5;
+  }
+};
+
+// Where the stages take their factors from: the table in memory, stage by
+// stage, or registers filled beforehand (Factors), which takes the table's
+// latency out of the transforms' serial chain.
+template <class T>
+struct Table {
+  const C2<T>* __restrict__ tw;
+  template <int N, int R, int P, int S>
+  __device__ __forceinline__ void get(C2<T> (&w)[4], int t) const {
+    load_factors<N, R, P>(w, tw, t);
+  }
+};
+template <int N, class T, int SCH = kSchedDefault>
+struct Factors {
+  C2<T> f[3][4];  // twiddled stages of sizes up to 1024
+  template <int P = 1, int S = 0>
+  __device__ __forceinline__ void load(const C2<T>* __restrict__ tw, int t) {
+    constexpr int R = stage_radix<N, SCH>(P);
+    if constexpr (P > 1) {
+      static_assert(S < 3, "stages");
+      load_factors<N, R, P>(f[S], tw, t);
+    }
+    if constexpr (P * R < N) load<P * R, (P > 1 ? S + 1 : 0)>(tw, t);
+  }
+  template <int, int, int, int S>
+  __device__ __forceinline__ void get(C2<T> (&w)[4], int) const {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) w[q] = f[S][q];
   }
 };
 
@@ -232,7 +277,7 @@ __device__ __forceinline__ void lds_sync() {
 // ---- one Stockham stage, recursing into the next ---------------------------
 // v[f][e] holds element t + e*TT of transform f.  `lds` points at this group's
 // fft_slots(NF) regions of Padded<N> entries each.  `tw[j]` = e^{-2 pi i j / N}.
-template <int N, int DIR, int NF, int P, class T, int SCH, bool WAVE>
+template <int N, int DIR, int NF, int P, class T, int SCH, bool WAVE, int S = 0>
 struct FftStage {
   static constexpr int E = kFftE;
   static constexpr int TT = N / E;
@@ -245,7 +290,7 @@ struct FftStage {
   // twiddle multiplication and radix-R DFT of the NB butterflies of transform
   // f; the outputs go back to registers (last stage) or to LDS region `slot`
   __device__ static __forceinline__ void butterflies(C2<T> (&v)[NF][E], int f, C2<T>* slot, int t,
-                                                     const C2<T>* __restrict__ tw) {
+                                                     const C2<T> (&w)[4]) {
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       const int i = t + b * TT;
@@ -254,7 +299,7 @@ struct FftStage {
 #pragma unroll
       for (int r = 0; r < R; ++r) u[r] = v[f][b + r * NB];
       if constexpr (P > 1)
-        DftTw<R, DIR, T>::template run<N>(u, tw, k * (N / (P * R)));
+        DftTw<R, DIR, T>::run(u, w, b);
       else
         Dft<R, DIR, T>::run(u);
       if constexpr (LAST) {
@@ -274,31 +319,34 @@ struct FftStage {
     for (int e = 0; e < E; ++e) v[f][e] = slot[j0 + lds_step<SCH>(e * TT)];
   }
 
-  __device__ static __forceinline__ void run(C2<T> (&v)[NF][E], C2<T>* lds, int t,
-                                             const C2<T>* __restrict__ tw) {
+  template <class F>
+  __device__ static __forceinline__ void run(C2<T> (&v)[NF][E], C2<T>* lds, int t, const F& tw) {
     constexpr int NS = fft_slots(NF, WAVE);
+    constexpr int SN = P > 1 ? S + 1 : 0;
+    C2<T> w[4];
+    if constexpr (P > 1) tw.template get<N, R, P, S>(w, t);
     if constexpr (LAST) {
 #pragma unroll
-      for (int f = 0; f < NF; ++f) butterflies(v, f, lds, t, tw);
+      for (int f = 0; f < NF; ++f) butterflies(v, f, lds, t, w);
     } else if constexpr (NS == NF) {
 #pragma unroll
-      for (int f = 0; f < NF; ++f) butterflies(v, f, lds + f * NP, t, tw);
+      for (int f = 0; f < NF; ++f) butterflies(v, f, lds + f * NP, t, w);
       lds_sync<WAVE>();
 #pragma unroll
       for (int f = 0; f < NF; ++f) gather(v, f, lds + f * NP, t);
       lds_sync<WAVE>();
-      FftStage<N, DIR, NF, P * R, T, SCH, WAVE>::run(v, lds, t, tw);
+      FftStage<N, DIR, NF, P * R, T, SCH, WAVE, SN>::run(v, lds, t, tw);
     } else {
       // transform f uses slot f % NS; the barrier after writing f also orders
       // every read of f - NS (issued before it) ahead of the reuse of its slot
 #pragma unroll
       for (int f = 0; f < NF; ++f) {
-        butterflies(v, f, lds + (f % NS) * NP, t, tw);
+        butterflies(v, f, lds + (f % NS) * NP, t, w);
         lds_sync<WAVE>();
         gather(v, f, lds + (f % NS) * NP, t);
       }
       lds_sync<WAVE>();
-      FftStage<N, DIR, NF, P * R, T, SCH, WAVE>::run(v, lds, t, tw);
+      FftStage<N, DIR, NF, P * R, T, SCH, WAVE, SN>::run(v, lds, t, tw);
     }
   }
 };
@@ -309,6 +357,11 @@ template <int N, int DIR, int NF, int SCH = kSchedDefault, bool WAVE = false, cl
 __device__ __forceinline__ void fft(C2<T> (&v)[NF][kFftE], C2<T>* lds, int t,
                                     const C2<T>* __restrict__ tw) {
   static_assert(N >= 64 && (N & (N - 1)) == 0, "N must be a power of two >= 64");
+  FftStage<N, DIR, NF, 1, T, SCH, WAVE>::run(v, lds, t, Table<T>{tw});
+}
+// the same with the factors at hand
+template <int N, int DIR, int NF, int SCH = kSchedDefault, bool WAVE = false, class T>
+__device__ __forceinline__ void fft(C2<T> (&v)[NF][kFftE], C2<T>* lds, int t, const Factors<N, T, SCH>& tw) {
   FftStage<N, DIR, NF, 1, T, SCH, WAVE>::run(v, lds, t, tw);
 }
 

@@ -213,6 +213,29 @@ __device__ __forceinline__ size_t mix_idx(int f, int m, int y) {
 // without, six paper-preset instances) than the second reads cost; up to 1024
 // points keeping them is the faster (radius sweep 69.7 against 71.5 us a step).
 constexpr int kReloadN = 2048;
+
+// A pass's factors: up to kPreloadN points loaded before its data, so that
+// their latency runs beside the data's instead of in each stage's serial
+// chain (a 512^2 circle alone 16.1 -> 15.7 us a step, the radius sweep 62.8 ->
+// 60.9, ten 512^2 FP64 instances 44.7 -> 42.2); beyond that the three or four
+// twiddled stages' factors would cost the registers that kReloadN frees.
+constexpr int kPreloadN = 1024;
+template <int N, class T, int SCH>
+struct StepFactors {
+  static constexpr bool PRE = N <= kPreloadN;
+  const C2<T>* tw;
+  Factors<N, T, SCH> f;
+  __device__ __forceinline__ StepFactors(const C2<T>* p, int t) : tw(p) {
+    if constexpr (PRE) f.load(p, t);
+  }
+  template <int DIR, int NF, bool WAVE, bool SECOND>
+  __device__ __forceinline__ void run(C2<T> (&v)[NF][kFftE], C2<T>* lds, int t) const {
+    if constexpr (PRE)
+      fft<N, DIR, NF, SCH, WAVE>(v, lds, t, f);
+    else
+      fft<N, DIR, NF, SCH, WAVE>(v, lds, t, reload<(SECOND && N >= kReloadN)>(tw));
+  }
+};
 template <bool FRESH, class T>
 __device__ __forceinline__ const C2<T>* reload(const C2<T>* tw) {
   if constexpr (FRESH) {
@@ -312,6 +335,8 @@ __device__ __forceinline__ void row_body(const C2<T>* __restrict__ X, C2<T>* __r
   const T* Kp = K + inst * N * N;
   C2<T>* L = lds + lane * RowSmem<N, RP, T, SCH>::LS;
 
+  const StepFactors<N, T, SCH> fac(tw, t);
+
   // gather Z(m) over the full row spectrum from the stored m_x = 0..M half
   C2<T> z[3][E];
 #pragma unroll
@@ -342,7 +367,7 @@ __device__ __forceinline__ void row_body(const C2<T>* __restrict__ X, C2<T>* __r
     z[1][e] = pack_pq(a.b, b.b);  // v_x + i v_y, row y0+1
     z[2][e] = pack_pq(w.a, w.b);  // omega(y0) + i omega(y0+1)
   }
-  fft<N, +1, 3, SCH, NT == 64>(z, L, t, tw);
+  fac.template run<+1, 3, NT == 64, false>(z, L, t);
 
   // mask rows, loaded after the inverse transforms: issued before them they
   // would hold 16 registers through the transforms (the row pass ran ~5 %
@@ -373,7 +398,7 @@ __device__ __forceinline__ void row_body(const C2<T>* __restrict__ X, C2<T>* __r
     if constexpr (GW)
       wv[NFY - 1][e] = mk(-c.gamma_w * kr[0][e] * z[2][e].x, -c.gamma_w * kr[1][e] * z[2][e].y);
   }
-  fft<N, -1, NFY, SCH, NT == 64>(wv, L, t, reload<(N >= kReloadN)>(tw));
+  fac.template run<-1, NFY, NT == 64, true>(wv, L, t);
 
 #pragma unroll
   for (int r = 0; r < 2; ++r)
@@ -524,15 +549,40 @@ __device__ __forceinline__ void col_body(const C2<T>* __restrict__ Y, C2<T>* __r
   C2<T>* fsp = (MODE >= 2) ? fst + inst * SLOTS * NFY * MP * SP : nullptr;  // kept forcing
   double sux = 0.0, suy = 0.0, sax = 0.0, say = 0.0;                       // kept k = 0 sums
 
+  const StepFactors<N, T, SCH> fac(tw, t);
   C2<T> f[NFY][E];
   double s1x = 0.0, s1y = 0.0;
   if constexpr (MODE != 1) {
+    const C2<T>* Yp = Y + inst * NFY * G::MP4 * N;
+    const T h = (T)0.5;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      C2<T> w0 = mk<T>(0, 0), w1 = mk<T>(0, 0);
+      if (valid) {
+        w0 = Yp[mix_idx<N>(0, mx, t + e * TT)];  // W(m_x) of row y
+        w1 = Yp[mix_idx<N>(1, mx, t + e * TT)];  // W(N - m_x) of row y
+      }
+      f[0][e] = mk(h * (w0.x + w1.x), h * (w0.y - w1.y));   // row transform of N_x
+      f[1][e] = mk(h * (w0.y + w1.y), -h * (w0.x - w1.x));  // row transform of N_y
+      if constexpr (GW) f[2][e] = valid ? Yp[mix_idx<N>(2, mx, t + e * TT)] : mk<T>(0, 0);
+    }
     if (tile == 0) {  // sum of the row sums: DFT of the k = 0 forcing
+      // (its loads all in flight at once: this tile is the last to finish
+      // when there are few others)
       const T* rs = rowsum + inst * 2 * N;
+      constexpr int RY = (N + NT - 1) / NT;
+      T ra[RY], rb[RY];
+#pragma unroll
+      for (int q = 0; q < RY; ++q) {
+        const int y = tid + q * NT;
+        ra[q] = y < N ? rs[y] : (T)0;
+        rb[q] = y < N ? rs[N + y] : (T)0;
+      }
       double a = 0.0, b = 0.0;
-      for (int y = tid; y < N; y += NT) {
-        a += (double)rs[y];
-        b += (double)rs[N + y];
+#pragma unroll
+      for (int q = 0; q < RY; ++q) {
+        a += (double)ra[q];
+        b += (double)rb[q];
       }
       a = wave_sum_from(a, 1);
       b = wave_sum_from(b, 1);
@@ -574,20 +624,7 @@ __device__ __forceinline__ void col_body(const C2<T>* __restrict__ Y, C2<T>* __r
         s1y -= s1st[2 * inst + 1];
       }
     }
-    const C2<T>* Yp = Y + inst * NFY * G::MP4 * N;
-    const T h = (T)0.5;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      C2<T> w0 = mk<T>(0, 0), w1 = mk<T>(0, 0);
-      if (valid) {
-        w0 = Yp[mix_idx<N>(0, mx, t + e * TT)];  // W(m_x) of row y
-        w1 = Yp[mix_idx<N>(1, mx, t + e * TT)];  // W(N - m_x) of row y
-      }
-      f[0][e] = mk(h * (w0.x + w1.x), h * (w0.y - w1.y));   // row transform of N_x
-      f[1][e] = mk(h * (w0.y + w1.y), -h * (w0.x - w1.x));  // row transform of N_y
-      if constexpr (GW) f[2][e] = valid ? Yp[mix_idx<N>(2, mx, t + e * TT)] : mk<T>(0, 0);
-    }
-    fft<N, -1, NFY, SCH, NT == 64>(f, L, t, tw);
+    fac.template run<-1, NFY, NT == 64, false>(f, L, t);
     if constexpr (MODE == 2 || MODE == 3) {  // keep (stage 1) or subtract (stage 2) the stage-1 forcing
 #pragma unroll
       for (int e = 0; e < E; ++e) {
@@ -752,7 +789,7 @@ __device__ __forceinline__ void col_body(const C2<T>* __restrict__ Y, C2<T>* __r
     z[1][e] = cvt<T>(cscale(ny[e], sN));
     z[2][e] = cvt<T>(mk(-cw.y * dk * sN, cw.x * dk * sN));
   }
-  fft<N, +1, 3, SCH, NT == 64>(z, L, t, reload<(N >= kReloadN)>(tw));
+  fac.template run<+1, 3, NT == 64, true>(z, L, t);
   if (valid) {
     C2<T>* Xp = X + inst * 3 * G::MP4 * N;
 #pragma unroll
