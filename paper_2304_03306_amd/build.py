@@ -54,6 +54,8 @@ def build(jobs: int | None = None, verbose: bool = True) -> Path:
     units += [(CSRC / "step_sched.hip", OUT / f"sched_{b}_{s}.o", [f"-DTTSH_BS={b}", f"-DTTSH_SCH={s}"])
               for b in BLOCKS for s in SCHED_VARIANTS]
     units += [(CSRC / "step_big.hip", OUT / f"big_{n}_{p}.o", [f"-DTTSH_N={n}", f"-DTTSH_PREC={p}"]) for n, p in BIG]
+    # the small sizes' resident time stepping
+    units += [(CSRC / "step_resident.hip", OUT / f"resident_{p}.o", [f"-DTTSH_PREC={p}"]) for p in PRECS]
     units.append((CSRC / "ttsh_capi.hip", OUT / "ttsh_capi.o", []))
     units.append((CSRC / "fno.hip", OUT / "fno.o", []))
     units.append((CSRC / "stream.hip", OUT / "stream.o", []))

@@ -57,6 +57,13 @@ struct BigOps {
 constexpr int kMaxBlockN = 2048;  // the largest size served by the 64..256-thread kernels
 const BigOps* big_ops(int N, int prec);  // null where the tiles do not fit (8192 in FP64)
 
+// `steps` one-stage time steps of class q of m in one launch, for the sizes
+// whose fields one workgroup holds (step_resident.hpp); hipErrorInvalidValue
+// for the others.
+hipError_t resident_32(const MultiArgs& m, int q, int gw, int steps, hipStream_t);
+hipError_t resident_64(const MultiArgs& m, int q, int gw, int steps, hipStream_t);
+hipError_t resident_96(const MultiArgs& m, int q, int gw, int steps, hipStream_t);
+
 const SizeOps* size_ops(int N);
 // record `msg` as the calling thread's last error (ttsh_last_error) and return code
 int record_error(int code, const char* msg);

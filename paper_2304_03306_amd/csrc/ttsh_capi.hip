@@ -483,6 +483,33 @@ hipError_t launch_col(ttsh_ctx* c, const MultiArgs& m, int mode, hipStream_t s) 
   return hipSuccess;
 }
 
+// Whether the steps run in resident workgroups (step_resident.hpp): one-stage
+// schemes on contexts whose every grid fits one workgroup's LDS.  64 points:
+// always (a step takes 7.3 us for 1 to 256 FP32 instances against 12.2 to 19.6
+// with the two passes, 9.8 against 28.5 for 256 in FP64).  128 points, FP32
+// transforms: a step takes 18 us up to 256 instances (one per compute unit,
+// bound by its vector instructions) and then grows with their number, while
+// the two passes take 13.5 us for 16, 17.6 for 64 and 45 for 256; the lines
+// cross near 70, so from 96 on.
+constexpr int kResident128 = 96;
+constexpr int kResidentSteps = 500;  // longest launch
+bool resident(const ttsh_ctx* c) {
+  if (c->p.scheme > TTSH_IMEX) return false;
+  for (auto& k : c->cls)
+    if (!(k.N == 64 || (k.N == 128 && c->prec != 64 && (int)k.ids.size() >= kResident128))) return false;
+  return true;
+}
+
+hipError_t launch_resident(ttsh_ctx* c, const MultiArgs& m, int steps, hipStream_t s) {
+  for (int q = 0; q < m.ncls; ++q) {
+    const hipError_t e = c->prec == 32   ? resident_32(m, q, c->gw, steps, s)
+                         : c->prec == 64 ? resident_64(m, q, c->gw, steps, s)
+                                         : resident_96(m, q, c->gw, steps, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_guard(ttsh_ctx* c, hipStream_t s, int g = 0, int G = 1);
 
 // n steps of group g of G on stream s
@@ -490,6 +517,18 @@ int enqueue_steps(ttsh_ctx* c, int64_t n, hipStream_t s, int g = 0, int G = 1) {
   if (n <= 0) return TTSH_OK;
   const MultiArgs r = group_args(c, 1, g, G), q = group_args(c, 0, g, G);
   if (r.ncls == 0) return TTSH_OK;
+  const bool check = c->guard && c->guard_every > 0;
+  if (resident(c)) {
+    // launches end where the guard looks at the states
+    for (int64_t i = 0; i < n;) {
+      const int64_t to = check ? std::min<int64_t>(n, i - i % c->guard_every + c->guard_every) : n;
+      const int k = (int)std::min<int64_t>(to - i, kResidentSteps);
+      HIPCHK(launch_resident(c, q, k, s));
+      i += k;
+      if (check && i % c->guard_every == 0) HIPCHK(launch_guard(c, s, g, G));
+    }
+    return TTSH_OK;
+  }
   // column-pass modes of one step, each after a row pass that evaluates the
   // forcing of the state the previous one left in X
   static const int one[] = {0}, etd2[] = {2, 3}, etd4[] = {4, 5, 6, 7};
@@ -504,7 +543,7 @@ int enqueue_steps(ttsh_ctx* c, int64_t n, hipStream_t s, int g = 0, int G = 1) {
     }
     // the guard after every guard_every steps of this sequence (inside a
     // captured chunk of G steps: after steps guard_every, 2 guard_every, ...)
-    if (c->guard && c->guard_every > 0 && (i + 1) % c->guard_every == 0) HIPCHK(launch_guard(c, s, g, G));
+    if (check && (i + 1) % c->guard_every == 0) HIPCHK(launch_guard(c, s, g, G));
   }
   return TTSH_OK;
 }
