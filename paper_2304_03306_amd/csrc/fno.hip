@@ -382,11 +382,6 @@ int kvec_ok(const Op& o, bool a_side) {
 
 
 // ---- element-wise kernels ------------------------------------------------------------------
-// y[j][i] = x[i][j] for an n x n matrix
-__global__ void k_transpose_bf16(const float* __restrict__ x, bf16* __restrict__ y, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n * n) y[(i % n) * n + i / n] = f2bf(x[i]);
-}
 __global__ void k_to_bf16(const float* __restrict__ x, bf16* __restrict__ y, long long n) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) y[i] = f2bf(x[i]);
@@ -1040,15 +1035,17 @@ __global__ void __launch_bounds__(256) k_mix(const bf16* __restrict__ G, const b
 // (operands transposed through the wavefront's LDS) and the bias gradients.
 // Each wavefront finally writes its sums to slot `wave` of part, laid out as
 // the gradient vector [dQ1 (C x HID) | db1 (HID) | dQ2 (HID x cout) | db2 (cout)],
-// and the slots are reduced afterwards in a fixed order.
+// and the slots are reduced afterwards in a fixed order.  MO is the number of
+// outputs the products are formed for (2 for the velocity increment: 712 us at
+// 256 x 128^2 points with the unused two summed as well, 665 without).
 constexpr int kProjBackMaxCout = 4;
-template <int C, int HID>
+template <int C, int HID, int MO>
 __global__ void __launch_bounds__(256, 2) k_proj_back(const bf16* __restrict__ h, const bf16* __restrict__ Q1,
                                                       const float* __restrict__ b1, const bf16* __restrict__ Q2,
                                                       const bf16* __restrict__ dy, int cout, bf16* __restrict__ dh,
                                                       float* __restrict__ part, long long npts) {
   static_assert(C == 32 && HID % 32 == 0, "k in steps of 32");
-  constexpr int HB = HID / 16, KB = C / 16, LDJ = HID + 8, LDC = C + 8, MO = kProjBackMaxCout;
+  constexpr int HB = HID / 16, KB = C / 16, LDJ = HID + 8, LDC = C + 8;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, l16 = lane & 15, q4 = (lane >> 4) * 4;
   const int q8 = (lane >> 4) * 8;  // k slots of the 32-deep products: q8 .. q8 + 7
   const long long wave = (long long)blockIdx.x * 4 + w, nwave = (long long)gridDim.x * 4;
@@ -1082,13 +1079,12 @@ __global__ void __launch_bounds__(256, 2) k_proj_back(const bf16* __restrict__ h
   bf16 *du_s = DU[w], *a_s = AA[w], *h_s = HS[w], *dy_s = DY[w];
   for (long long t = wave; t * 16 < npts; t += nwave) {
     const long long p = t * 16 + l16;
-    const bool ok = p < npts;
-    const short8_t hv = ok ? *(const short8_t*)(h + p * C + q8) : short8_t{0, 0, 0, 0, 0, 0, 0, 0};
+    const short8_t hv = *(const short8_t*)(h + p * C + q8);  // npts is a multiple of 16: every group is whole
     float dyv[MO];  // this lane's point
 #pragma unroll
-    for (int o = 0; o < MO; ++o) dyv[o] = (ok && o < cout) ? bf2f(dy[p * cout + o]) : 0.f;
+    for (int o = 0; o < MO; ++o) dyv[o] = o < cout ? bf2f(dy[p * cout + o]) : 0.f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) dy_s[l16 * 16 + q4 + e] = (ok && q4 + e < cout) ? dy[p * cout + q4 + e] : (bf16)0;
+    for (int e = 0; e < 4; ++e) dy_s[l16 * 16 + q4 + e] = q4 + e < cout ? dy[p * cout + q4 + e] : (bf16)0;
     *(short8_t*)(h_s + l16 * LDC + q8) = hv;
 #pragma unroll
     for (int hb = 0; hb < HB; ++hb) {
@@ -1102,8 +1098,8 @@ __global__ void __launch_bounds__(256, 2) k_proj_back(const bf16* __restrict__ h
         float da = 0.f;
 #pragma unroll
         for (int o = 0; o < MO; ++o) da += dyv[o] * Q2s[j][o];
-        a4[e] = ok ? uv * ph : 0.f;
-        d4[e] = ok ? da * (ph + uv * 0.39894228040143268f * __expf(-0.5f * uv * uv)) : 0.f;
+        a4[e] = uv * ph;
+        d4[e] = da * (ph + uv * 0.39894228040143268f * __expf(-0.5f * uv * uv));
       }
       const short4_t duf = pack4(d4[0], d4[1], d4[2], d4[3]);
       // rows = points, for dh below and the weight gradients
@@ -1122,7 +1118,7 @@ __global__ void __launch_bounds__(256, 2) k_proj_back(const bf16* __restrict__ h
       for (int hp = 0; hp < HID / 32; ++hp)
         d = mfma32(*(const short8_t*)(Q1s + (16 * cb + l16) * LDJ + 32 * hp + q8),
                    *(const short8_t*)(du_s + l16 * LDJ + 32 * hp + q8), d);
-      if (ok) *(short4_t*)(dh + p * C + 16 * cb + q4) = pack4(d[0], d[1], d[2], d[3]);
+      *(short4_t*)(dh + p * C + 16 * cb + q4) = pack4(d[0], d[1], d[2], d[3]);
     }
     // weight gradients: contraction over the group's 16 points (16 deep)
     short4_t hT[KB], dyb;
@@ -1180,6 +1176,59 @@ __global__ void __launch_bounds__(256, 2) k_proj_back(const bf16* __restrict__ h
     }
   }
   if (q4 == 0 && l16 < cout) slot[C * HID + HID + HID * cout + l16] = gb2;
+}
+
+// Gradient of the mode matrices for C = 32, one mode (k_x, q) per workgroup:
+//   dR_r = F_r^T g_r + F_i^T g_i,  dR_i = F_r^T g_i - F_i^T g_r
+// contracted over the batch, F and g in the mode layout [m][4m][B][C] (rows q
+// real, 2m + q imaginary).  Chunks of 64 samples are transposed into LDS, and
+// each of the four wavefronts forms one 16 x 16 block of both results from
+// one read of F and g (two products over the whole arrays read everything
+// twice: 52 us per layer at 256 samples, 9 us in one).
+__global__ void __launch_bounds__(256) k_mode_wgrad(const bf16* __restrict__ F, const bf16* __restrict__ g, int B, int m,
+                                                    float* __restrict__ dRr, float* __restrict__ dRi) {
+  constexpr int C = 32, KC = 64, LD = KC + 8;
+  __shared__ __align__(16) bf16 S[4][C * LD];  // F_r, F_i, g_r, g_i: [channel][sample]
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l16 = lane & 15, q4 = (lane >> 4) * 4;
+  const int q8 = (lane >> 4) * 8;
+  const int kx = blockIdx.x / (2 * m), q = blockIdx.x - kx * 2 * m;
+  const long long re = ((long long)kx * 4 * m + q) * B * C, im = re + 2LL * m * B * C;
+  const bf16* src[4] = {F + re, F + im, g + re, g + im};
+  const int bs = tid & 63, c0 = (tid >> 6) * 8;  // this thread's sample of a chunk and its eight channels
+  const int i0 = (w >> 1) * 16, j0 = (w & 1) * 16;
+  float4_t rr = {0.f, 0.f, 0.f, 0.f}, ii = rr, ri = rr, ir = rr;
+  for (int b0 = 0; b0 < B; b0 += KC) {
+    uint4 v[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      v[a] = b0 + bs < B ? *(const uint4*)(src[a] + (long long)(b0 + bs) * C + c0) : make_uint4(0, 0, 0, 0);
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const bf16* e = (const bf16*)&v[a];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) S[a][(c0 + k) * LD + bs] = e[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < KC; k += 32) {
+      const short8_t fr = *(const short8_t*)(S[0] + (i0 + l16) * LD + k + q8);
+      const short8_t fi = *(const short8_t*)(S[1] + (i0 + l16) * LD + k + q8);
+      const short8_t gr = *(const short8_t*)(S[2] + (j0 + l16) * LD + k + q8);
+      const short8_t gi = *(const short8_t*)(S[3] + (j0 + l16) * LD + k + q8);
+      rr = mfma32(fr, gr, rr);
+      ii = mfma32(fi, gi, ii);
+      ri = mfma32(fr, gi, ri);
+      ir = mfma32(fi, gr, ir);
+    }
+  }
+  const long long o = ((long long)q * m + kx) * C * C;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const long long at = o + (i0 + q4 + e) * C + j0 + l16;
+    dRr[at] = rr[e] + ii[e];
+    dRi[at] = ri[e] - ir[e];
+  }
 }
 
 // dz = dh * GELU'(z), eight elements per thread with 16-byte accesses (n % 8 == 0)
@@ -1511,6 +1560,66 @@ __global__ void k_build_wb(const float* __restrict__ Rr, const float* __restrict
   WbT[(mode * C2 + j) * C2 + i] = f2bf(v);
 }
 
+// The BF16 compute copies of every master parameter in one launch.
+struct Refresh {
+  const float* th;
+  long long oPw, oQ1, oQ2, oR[16], oW[16];
+  bf16 *Pw, *Q1, *Q2, *Wl[16], *WlT[16], *Wb[16], *WbT[16];
+  int L, m, C, cin, hid, cout;
+};
+// Workgroups 0 .. L 2m^2 - 1 (with modes: C = 32) build one mode's
+// Wb[kx][q] = [[R_r, R_i], [-R_i, R_r]] and its transpose, both written as
+// 16-byte rows from the two 32 x 32 blocks in LDS; the others convert the
+// small matrices.  (One element per thread with the transpose scattered took
+// 16 us per layer and 11 further launches; 118 us in all, 11 us now for four layers.)
+__global__ void __launch_bounds__(256) k_refresh(Refresh a, int modes) {
+  constexpr int C = 32;
+  __shared__ float R[2][C][C + 1];
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x < modes) {
+    const int per = 2 * a.m * a.m, l = blockIdx.x / per, mode = blockIdx.x - l * per;  // mode = kx 2m + q
+    const int kx = mode / (2 * a.m), q = mode - kx * 2 * a.m;
+    const float* src = a.th + a.oR[l] + ((long long)q * a.m + kx) * C * C;
+    const long long nR = 2LL * a.m * a.m * C * C;
+    for (int k = tid; k < C * C; k += 256) {
+      R[0][k / C][k % C] = src[k];
+      R[1][k / C][k % C] = src[nR + k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = tid; k < 2 * C * 2 * C / 8; k += 256) {
+      const int i = k / (2 * C / 8), j0 = (k % (2 * C / 8)) * 8;  // row i, columns j0 .. j0 + 7
+      bf16 o[8], t[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int j = j0 + e, ii = i % C, jj = j % C;
+        const bool im = (i < C) != (j < C);
+        const float x = R[im][ii][jj], y = R[im][jj][ii];
+        o[e] = f2bf(im && i >= C ? -x : x);  // Wb[i][j]
+        t[e] = f2bf(im && j >= C ? -y : y);  // Wb[j][i]
+      }
+      const long long at = ((long long)mode * 2 * C + i) * 2 * C + j0;
+      *(uint4*)(a.Wb[l] + at) = *(const uint4*)o;
+      *(uint4*)(a.WbT[l] + at) = *(const uint4*)t;
+    }
+    return;
+  }
+  const int n1 = a.cin * a.C, n2 = a.C * a.hid, n3 = a.hid * a.cout, nw = a.C * a.C;
+  int k = ((int)blockIdx.x - modes) * 256 + tid;
+  if (k < n1) {
+    a.Pw[k] = f2bf(a.th[a.oPw + k]);
+  } else if ((k -= n1) < n2) {
+    a.Q1[k] = f2bf(a.th[a.oQ1 + k]);
+  } else if ((k -= n2) < n3) {
+    a.Q2[k] = f2bf(a.th[a.oQ2 + k]);
+  } else if ((k -= n3) < a.L * nw) {
+    const int l = k / nw, r = k - l * nw;
+    const bf16 v = f2bf(a.th[a.oW[l] + r]);
+    a.Wl[l][r] = v;
+    a.WlT[l][(r % a.C) * a.C + r / a.C] = v;
+  }
+}
+
 unsigned nb(long long n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
 }  // namespace
@@ -1654,22 +1763,23 @@ int make_dft(fno_ctx* c) {
 // bf16 compute copies of the master parameters
 int refresh_weights(fno_ctx* c) {
   const int C = c->C, m = c->m;
-  hipLaunchKernelGGL(k_to_bf16, dim3(nb((long long)c->cin * C)), dim3(256), 0, c->s, c->theta + c->oPw, c->Pw,
-                     (long long)c->cin * C);
+  Refresh r{};
+  r.th = c->theta;
+  r.oPw = c->oPw; r.oQ1 = c->oQ1; r.oQ2 = c->oQ2;
+  r.Pw = c->Pw; r.Q1 = c->Q1; r.Q2 = c->Q2;
+  r.L = c->L; r.m = m; r.C = C; r.cin = c->cin; r.hid = c->hid; r.cout = c->cout;
   for (int l = 0; l < c->L; ++l) {
-    hipLaunchKernelGGL(k_to_bf16, dim3(nb((long long)C * C)), dim3(256), 0, c->s, c->theta + c->oW[l], c->Wl[l],
-                       (long long)C * C);
-    hipLaunchKernelGGL(k_transpose_bf16, dim3(nb((long long)C * C)), dim3(256), 0, c->s, c->theta + c->oW[l],
-                       c->WlT[l], C);
-    const long long nwb = (long long)2 * m * m * 4 * C * C;
-    const long long nR = (long long)2 * m * m * C * C;
-    hipLaunchKernelGGL(k_build_wb, dim3(nb(nwb)), dim3(256), 0, c->s, c->theta + c->oR[l], c->theta + c->oR[l] + nR,
-                       c->Wb[l], c->WbT[l], m, C);
+    r.oR[l] = c->oR[l]; r.oW[l] = c->oW[l];
+    r.Wl[l] = c->Wl[l]; r.WlT[l] = c->WlT[l]; r.Wb[l] = c->Wb[l]; r.WbT[l] = c->WbT[l];
+    if (C != 32) {
+      const long long nwb = (long long)2 * m * m * 4 * C * C, nR = (long long)2 * m * m * C * C;
+      hipLaunchKernelGGL(k_build_wb, dim3(nb(nwb)), dim3(256), 0, c->s, c->theta + c->oR[l], c->theta + c->oR[l] + nR,
+                         c->Wb[l], c->WbT[l], m, C);
+    }
   }
-  hipLaunchKernelGGL(k_to_bf16, dim3(nb((long long)C * c->hid)), dim3(256), 0, c->s, c->theta + c->oQ1, c->Q1,
-                     (long long)C * c->hid);
-  hipLaunchKernelGGL(k_to_bf16, dim3(nb((long long)c->hid * c->cout)), dim3(256), 0, c->s, c->theta + c->oQ2, c->Q2,
-                     (long long)c->hid * c->cout);
+  const int modes = C == 32 ? c->L * 2 * m * m : 0;
+  const long long small = (long long)c->cin * C + (long long)C * c->hid + (long long)c->hid * c->cout + (long long)c->L * C * C;
+  hipLaunchKernelGGL(k_refresh, dim3(modes + nb(small)), dim3(256), 0, c->s, r, modes);
   FCHK(hipGetLastError());
   return TTSH_OK;
 }
@@ -2345,11 +2455,15 @@ int fno_backward(fno_ctx* c, int B) {
     const long long groups = (P + 15) / 16;
     const long long blocks = std::max<long long>(1, std::min<long long>({(groups + 3) / 4, 512, (long long)c->part_n / (4 * S)}));
     const std::pair<const char*, size_t>* none = nullptr;
-    if ((long long)c->part_n < 4 * S || !inside(c, c->h[c->L], P * C - 1, 2, none, 0) ||
+    if (P % 16 || (long long)c->part_n < 4 * S || !inside(c, c->h[c->L], P * C - 1, 2, none, 0) ||
         !inside(c, c->dy, P * co - 1, 2, none, 0) || !inside(c, c->dh0, P * C - 1, 2, none, 0))
       return ffail(TTSH_EINVAL, "projection backward operand out of bounds (internal layout error)");
-    hipLaunchKernelGGL((k_proj_back<32, 128>), dim3((unsigned)blocks), dim3(256), 0, c->s, c->h[c->L], c->Q1,
-                       c->theta + c->oQ1b, c->Q2, c->dy, co, c->dh0, c->part, P);
+    if (co <= 2)
+      hipLaunchKernelGGL((k_proj_back<32, 128, 2>), dim3((unsigned)blocks), dim3(256), 0, c->s, c->h[c->L], c->Q1,
+                         c->theta + c->oQ1b, c->Q2, c->dy, co, c->dh0, c->part, P);
+    else
+      hipLaunchKernelGGL((k_proj_back<32, 128, kProjBackMaxCout>), dim3((unsigned)blocks), dim3(256), 0, c->s,
+                         c->h[c->L], c->Q1, c->theta + c->oQ1b, c->Q2, c->dy, co, c->dh0, c->part, P);
     FCHK(hipGetLastError());
     if ((rc = reduce_parts(c, c->part, blocks * 4, S, c->grad + c->oQ1))) return rc;
   } else {
@@ -2400,6 +2514,16 @@ int fno_backward(fno_ctx* c, int B) {
     if ((rc = cap_copy(c, c->capGG[l], c->gG, (long long)m * 4 * m * B * C))) return rc;
     // dR per mode (kx, q): dR_r = F_r^T gG_r + F_i^T gG_i ; dR_i = F_r^T gG_i - F_i^T gG_r
     const long long nR = 2LL * m * m * C * C;
+    if (c->specialized && C == 32) {
+      const std::pair<const char*, size_t>* none = nullptr;
+      const long long modes = 2LL * m * m;
+      if (!inside(c, c->G[l], modes * 2 * B * C - 1, 2, none, 0) || !inside(c, c->gG, modes * 2 * B * C - 1, 2, none, 0) ||
+          !inside(c, c->grad + c->oR[l], 2 * nR - 1, 4, none, 0))
+        return ffail(TTSH_EINVAL, "mode gradient operand out of bounds (internal layout error)");
+      hipLaunchKernelGGL(k_mode_wgrad, dim3((unsigned)modes), dim3(256), 0, c->s, c->G[l], c->gG, B, m,
+                         c->grad + c->oR[l], c->grad + c->oR[l] + nR);
+      FCHK(hipGetLastError());
+    } else {
     for (int part = 0; part < 2; ++part) {
       GemmArgs r = ga();
       r.M = C; r.N = C; r.K = B; r.K2 = B;
@@ -2418,6 +2542,7 @@ int fno_backward(fno_ctx* c, int B) {
       r.C = c->grad + c->oR[l] + part * nR; r.c_bf16 = 0;
       r.sC1 = (long long)C * C; r.sC2 = (long long)m * C * C; r.rC = C; r.cC = 1;
       if ((rc = cgemm(c, r))) return rc;
+    }
     }
     // g_F = g_G Wb^T  (into gF, mode layout [m][2m][B][2C])
     if ((rc = spectral_mix(c, c->gG, c->Wb[l], c->WbT[l], true, c->gF, B))) return rc;
