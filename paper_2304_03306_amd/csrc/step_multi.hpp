@@ -164,8 +164,15 @@ __global__ void __launch_bounds__(BS) col_multi(MultiArgs a) {
 // tile decode is constant; the autotuner picks this or the multi-size launch.
 // Grids of 2048 points are served only here (their tiles would raise the
 // register budget of the multi-size kernels for every other size).
+// Wavefronts per SIMD the compiler has to make room for: two of 4096 points'
+// 512-thread FP32 workgroups share a compute unit with 128 registers each
+// (the column pass with the vorticity source would take 131 and run alone).
+template <int N, class T>
+constexpr int min_waves() {
+  return N == 4096 && sizeof(T) == 4 ? 4 : 1;
+}
 template <int N, class T, bool GW, int BS>
-__global__ void __launch_bounds__(BS) row_one(MultiArgs a) {
+__global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(min_waves<N, T>()))) row_one(MultiArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int b = xcd_remap(blockIdx.x, gridDim.x);
   const ClassArgs& d = a.c[0];
@@ -176,7 +183,7 @@ __global__ void __launch_bounds__(BS) row_one(MultiArgs a) {
 }
 
 template <int N, class T, class S, bool GW, int MODE, int BS>
-__global__ void __launch_bounds__(BS) col_one(MultiArgs a) {
+__global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(min_waves<N, T>()))) col_one(MultiArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int b = xcd_remap(blockIdx.x, gridDim.x);
   const ClassArgs& d = a.c[0];
