@@ -202,39 +202,7 @@ __global__ void k_resample(const C2<S>* __restrict__ src, int Ns, C2<double>* __
   dst[i] = v;
 }
 
-// ---- order parameters and defects of the real-space fields --------------------
-// Combines the row kernel's partials (kOrderPart values per workgroup: sums of
-// |e_theta . v| and |v|, and per region the largest |omega| with its node and
-// value) into out[0] = Psi (paper's normalisation) and out[1] = Psi_2 =
-// |w_l + w_r| / (|w_l| + |w_r|), NaN for an empty region.  Thread t takes the
-// workgroups t, t + 256, ... in order and the threads are combined by a tree,
-// so that results do not vary between runs.
-__global__ void __launch_bounds__(256) k_order_final(const double* __restrict__ part, int nb,
-                                                     double* __restrict__ out) {
-  __shared__ double red[256][kOrderPart];
-  const int t = threadIdx.x;
-  double* a = red[t];
-  for (int q = 0; q < kOrderPart; ++q) a[q] = 0.0;
-  a[2] = a[5] = -1.0;
-  auto add = [&](const double* p) {
-    a[0] += p[0];
-    a[1] += p[1];
-    for (int s = 2; s < kOrderPart; s += 3) order_best(a[s], a[s + 1], a[s + 2], p[s], p[s + 1], p[s + 2]);
-  };
-  for (int q = t; q < nb; q += 256) add(part + (size_t)q * kOrderPart);
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (t < o) add(red[t + o]);
-    __syncthreads();
-  }
-  if (t == 0) {
-    const double two_pi = 2.0 / M_PI;
-    out[0] = (a[0] / a[1] - two_pi) / (1.0 - two_pi);
-    const double wl = a[4], wr = a[7];
-    out[1] = (a[2] < 0.0 || a[5] < 0.0) ? __builtin_nan("") : fabs(wl + wr) / (fabs(wl) + fabs(wr));
-  }
-}
-
+// ---- defects of the real-space fields -----------------------------------------
 // The counts over the N^2 nodes run in order_blocks(N) workgroups of 1024
 // threads, each writing one partial result.
 constexpr int kOrderMaxBlocks = 256;

@@ -120,7 +120,7 @@ struct RowsOut {
 constexpr int kOrderPart = 8;
 
 // The larger |omega| of two candidates; equal values go to the lower node.
-__device__ __forceinline__ void order_best(double& a, double& i, double& w, double a2, double i2, double w2) {
+__host__ __device__ __forceinline__ void order_best(double& a, double& i, double& w, double a2, double i2, double w2) {
   if (a2 > a || (a2 == a && a2 >= 0.0 && i2 < i)) {
     a = a2;
     i = i2;

@@ -215,8 +215,8 @@ struct ttsh_ctx {
   int guard_every = 50;                  // steps between guard checks inside ttsh_step (0: only at ttsh_sync)
   void* pb = nullptr;                    // batched coarse-field columns (grown on demand)
   size_t pb_cap = 0;                     // its bytes
-  double* pnorm = nullptr;               // [pnorm_cap][2]
-  size_t pnorm_cap = 0;
+  double* pin = nullptr;                 // pinned host memory that kernels write partial results to
+  size_t pin_cap = 0;                    // its values (grown on demand)
   void* lyq = nullptr;                   // Lyapunov vectors: kMaxLyap logs, then [p][state] FP64
   size_t lyq_cap = 0;                    // bytes
   double* psdf = nullptr;                // PSD frequencies [kMaxPsdFreqs], then S [kMaxPsdFreqs]
@@ -630,6 +630,19 @@ int twiddles64(ttsh_ctx* c, int N, const void** out) {
   return TTSH_OK;
 }
 
+// room for n values of pinned host memory in c->pin (only between
+// synchronisations: its users wait for their kernels before they return)
+int need_pinned(ttsh_ctx* c, size_t n) {
+  if (n <= c->pin_cap) return TTSH_OK;
+  if (c->pin) HIPCHK(hipHostFree(c->pin));
+  c->pin = nullptr;
+  c->pin_cap = 0;
+  if (hipHostMalloc((void**)&c->pin, n * sizeof(double), hipHostMallocDefault) != hipSuccess)
+    return fail(TTSH_ENOMEM, "pinned host memory");
+  c->pin_cap = n;
+  return TTSH_OK;
+}
+
 // The columns of an instance's fields on an N grid, transformed along y into
 // G ((N/4+1) x N entries of the components of `comp`, at most 12 N^2 + 48 N
 // bytes); N may differ from the instance's own grid.
@@ -868,8 +881,9 @@ void free_ctx(ttsh_ctx* c) {
   if (c->scr1) hipFree(c->scr1);
   if (c->dnorm) hipFree(c->dnorm);
   if (c->dflags) hipFree(c->dflags);
-  for (void* p : {c->pb, (void*)c->pnorm, c->lyq, (void*)c->psdf})
+  for (void* p : {c->pb, c->lyq, (void*)c->psdf})
     if (p) hipFree(p);
+  if (c->pin) hipHostFree(c->pin);
   if (c->cap) hipStreamDestroy(c->cap);
   for (int g = 0; g < kMaxGroups; ++g) {
     if (c->gstream[g]) hipStreamDestroy(c->gstream[g]);
@@ -1253,19 +1267,13 @@ int ttsh_project_coarse(ttsh_ctx* c, int N, float* v, int64_t pix_stride, int ba
     c->pb_cap = bytes;
   }
   const size_t parts = (size_t)batch * ops->col_groups;
-  if (norms && parts > c->pnorm_cap) {
-    if (c->pnorm) hipFree(c->pnorm);
-    c->pnorm = nullptr;
-    c->pnorm_cap = 0;
-    if (hipMalloc((void**)&c->pnorm, sizeof(double) * 2 * parts) != hipSuccess)
-      return fail(TTSH_ENOMEM, "norm buffer");
-    c->pnorm_cap = parts;
-  }
+  if (norms)
+    if (int e = need_pinned(c, 2 * parts)) return e;
   int rc;
   const void* tw = nullptr;
   if ((rc = twiddles64(c, N, &tw))) return rc;
   HIPCHK(ops->project_rows(v, (long long)pix_stride, batch, c->pb, tw, c->stream));
-  HIPCHK(ops->project_cols(c->pb, batch, norms ? c->pnorm : nullptr, tw, c->stream));
+  HIPCHK(ops->project_cols(c->pb, batch, norms ? c->pin : nullptr, tw, c->stream));
   RowsOut a{};
   a.G = (const C2<double>*)c->pb;
   a.tw = (const C2<double>*)tw;
@@ -1278,9 +1286,8 @@ int ttsh_project_coarse(ttsh_ctx* c, int N, float* v, int64_t pix_stride, int ba
   a.vec = pix_stride % 2 == 0 && ((uintptr_t)v & 7) == 0;
   HIPCHK(ops->synth_rows(a, c->stream));
   if (norms) {
-    std::vector<double> h(2 * parts);
-    HIPCHK(hipMemcpyAsync(h.data(), c->pnorm, sizeof(double) * h.size(), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
+    const double* h = c->pin;
     for (int b = 0; b < batch; ++b) {
       double e = 0.0, w = 0.0;
       for (int g = 0; g < ops->col_groups; ++g) {
@@ -1294,9 +1301,10 @@ int ttsh_project_coarse(ttsh_ctx* c, int N, float* v, int64_t pix_stride, int ba
   return TTSH_OK;
 }
 
-// Order parameters into dnorm[0] (Psi, from the velocity) and dnorm[1] (Psi_2,
-// from the vorticity), the first from_what of them skipped; the host receives
-// dnorm[from_what..1] in out[0..].
+// Order parameters Psi (from the velocity) and Psi_2 (from the vorticity), the
+// first from_what of them skipped.  The row kernel's workgroups write their
+// partials to pinned host memory, and the host adds them up in workgroup
+// order: a further kernel and a copy for a few kilobytes took longer.
 static int order_impl(ttsh_ctx* c, int inst, double cx, double cy, double D, int from_what, double* out) {
   const int N = c->N[inst], comp = from_what == 0 ? kCompVW : kCompW;
   int rc;
@@ -1307,14 +1315,24 @@ static int order_impl(ttsh_ctx* c, int inst, double cx, double cy, double D, int
   a.cx = cx;
   a.cy = cy;
   a.D = D;
-  a.out = c->scr1;  // partials, kOrderPart values per workgroup
+  const int nb = size_ops(N)->row_groups;
+  if ((rc = need_pinned(c, (size_t)nb * kOrderPart))) return rc;
+  a.out = c->pin;
   HIPCHK(size_ops(N)->synth_rows(a, c->stream));
-  hipLaunchKernelGGL(k_order_final, dim3(1), dim3(256), 0, c->stream, (const double*)c->scr1, size_ops(N)->row_groups,
-                     c->dnorm);
-  HIPCHK(hipGetLastError());
-  HIPCHK(hipMemcpyAsync(out, c->dnorm + from_what, (2 - from_what) * sizeof(double), hipMemcpyDeviceToHost,
-                        c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
+  double num = 0.0, den = 0.0, best[2] = {-1.0, -1.0}, node[2] = {0.0, 0.0}, w[2] = {0.0, 0.0};
+  for (int b = 0; b < nb; ++b) {
+    const double* p = c->pin + (size_t)b * kOrderPart;
+    num += p[0];
+    den += p[1];
+    for (int s = 0; s < 2; ++s) order_best(best[s], node[s], w[s], p[2 + 3 * s], p[3 + 3 * s], p[4 + 3 * s]);
+  }
+  if (from_what == 0) {
+    const double two_pi = 2.0 / M_PI;
+    *out++ = (num / den - two_pi) / (1.0 - two_pi);
+  }
+  // an empty region gives NaN
+  *out = (best[0] < 0.0 || best[1] < 0.0) ? std::nan("") : std::fabs(w[0] + w[1]) / (std::fabs(w[0]) + std::fabs(w[1]));
   return TTSH_OK;
 }
 
