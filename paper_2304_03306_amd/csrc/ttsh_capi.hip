@@ -338,8 +338,18 @@ bool bs_valid(const ttsh_ctx* c, int bs) {
   return true;
 }
 
-// Default workgroup size: the largest one that still gives >= 2048 row-pass
-// workgroups (8 per compute unit), else the smallest usable one.
+// Default workgroup sizes, where no tuning was set.
+// Row pass: the smallest usable one; a one-wavefront tile needs no barrier and
+// a 128-thread one a cheap one, and either was within 4 % of the fastest for
+// 0.25e6 to 16e6 points of 128^2 to 1024^2 grids.
+// Column pass: tiles of one column below 2^19 points (one 512^2 circle: as many
+// tiles as there can be), of two columns from there (15 x 512^2: 39 us a step
+// with one, 34 with two), of four from 2^23 points on in FP32, where whole
+// 32-byte runs of the mixed-domain arrays count (61 x 512^2 102 us with two, 97
+// with four; 244 x 256^2 107 and 96).  FP64 tiles of four lose residency (61 x
+// 256^2: 62 us with two columns, 65 with four).  The rule before took the
+// largest size that still gave 2048 row tiles for both passes: 154 us for 244 x
+// 256^2, 117 for 61 x 512^2.
 int choose_bs(ttsh_ctx* c) {
   if (c->opt_bs) {
     if (!bs_valid(c, c->opt_bs)) return fail(TTSH_EUNSUPPORTED, "workgroup size not usable for this context");
@@ -348,13 +358,16 @@ int choose_bs(ttsh_ctx* c) {
   }
   long pts = 0;
   for (size_t i = 0; i < c->N.size(); ++i) pts += (long)c->N[i] * c->N[i];
-  int best = 0;
+  const int columns = c->prec == 64 ? (pts <= (1L << 21) ? 1 : 2) : pts < (1L << 19) ? 1 : pts < (1L << 23) ? 2 : 4;
+  int row = 0, col = 0;
   for (int bs : {64, 128, 256}) {
     if (!bs_valid(c, bs)) continue;
-    if (!best || pts / (16L * bs) >= 2048) best = bs;
+    if (!row) row = bs;
+    if (!col || 8 * col < columns * max_small_N(c)) col = bs;
   }
-  if (!best) return fail(TTSH_EUNSUPPORTED, "no workgroup size fits N");
-  c->bs = c->bs_row = best;
+  if (!row) return fail(TTSH_EUNSUPPORTED, "no workgroup size fits N");
+  c->bs_row = row;
+  c->bs = col;
   return TTSH_OK;
 }
 
@@ -440,6 +453,11 @@ MultiArgs multi_args(ttsh_ctx* c, int row, int inst) {
 // kernels are not compiled for that size)
 bool must_split(const ttsh_ctx* c) { return max_N(c) > 1024; }
 
+// A context of one grid size takes that size's own kernels, whose registers
+// are not those of the largest grid (3 to 6 % faster steps), unless a transform
+// schedule was chosen that only the multi-size kernels have.
+bool one_size(const ttsh_ctx* c, int sched) { return c->cls.size() == 1 && (sched == kSchedDefault || c->prec != 32); }
+
 // a non-default transform schedule exists for the multi-size launches of the
 // FP32 arithmetic (row pass, one-stage column pass)
 bool sched_usable(const ttsh_ctx* c, int split) { return c->prec == 32 && !split && !must_split(c); }
@@ -455,7 +473,7 @@ MultiArgs only_class(const MultiArgs& m, int q) {
 }
 
 hipError_t launch_row(ttsh_ctx* c, const MultiArgs& m, hipStream_t s) {
-  const bool split = c->split_row || must_split(c);
+  const bool split = c->split_row || must_split(c) || one_size(c, c->sched_row);
   if (c->sched_row != kSchedDefault && sched_usable(c, split))
     return sched_ops(c->bs_row, c->sched_row)->row(m, c->gw, s);
   const int tp = c->prec == 64 ? 64 : 32;  // the row pass depends on the transform precision only
@@ -469,7 +487,7 @@ hipError_t launch_row(ttsh_ctx* c, const MultiArgs& m, hipStream_t s) {
   return hipSuccess;
 }
 hipError_t launch_col(ttsh_ctx* c, const MultiArgs& m, int mode, hipStream_t s) {
-  const bool split = c->split_col || must_split(c);
+  const bool split = c->split_col || must_split(c) || one_size(c, c->sched_col);
   if (mode == 0 && c->sched_col != kSchedDefault && sched_usable(c, split))
     return sched_ops(c->bs, c->sched_col)->col(m, c->gw, s);
   const MultiOps* o = multi_ops(c->prec, c->bs);
