@@ -1027,7 +1027,9 @@ int ttsh_create(ttsh_ctx** out, int n_inst, const int* N, const double* L, const
   if (hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking) != hipSuccess)
     return bail(fail(TTSH_EHIP, "stream creation failed"));
   if (sizes.size() > (size_t)kMaxClasses) return bail(fail(TTSH_EUNSUPPORTED, "too many grid sizes"));
-  int rc = choose_bs(c);
+  int rc = need_pinned(c, 8192);  // enough for the common read-outs' first call
+  if (rc) return bail(rc);
+  rc = choose_bs(c);
   if (rc) return bail(rc);
   *out = c;
   return TTSH_OK;
