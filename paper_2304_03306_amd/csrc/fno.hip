@@ -387,6 +387,15 @@ __global__ void k_to_bf16(const float* __restrict__ x, bf16* __restrict__ y, lon
   if (i < n) y[i] = f2bf(x[i]);
 }
 
+// the same for 16-byte aligned arrays, eight values per thread (the network's
+// input: 28 us for 256 x 128^2 x 3 values one by one, 16 us so)
+__global__ void __launch_bounds__(256) k_to_bf16x8(const float4* __restrict__ x, uint4* __restrict__ y, long long n8) {
+  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n8) return;
+  const float4 a = x[2 * i], b = x[2 * i + 1];
+  y[i] = make_uint4(pack2(a.x, a.y), pack2(a.z, a.w), pack2(b.x, b.y), pack2(b.z, b.w));
+}
+
 // h0[p][c] = sum_k x[p][k] P_w[k][c] + P_b[c]  (cin is small: vector ALU)
 __global__ void k_lift(const bf16* __restrict__ x, const bf16* __restrict__ Pw,
                        const float* __restrict__ Pb, bf16* __restrict__ h, long long npts, int cin, int C) {
@@ -2332,7 +2341,11 @@ int fno_forward_ex(fno_ctx* c, const float* x, float* y, int64_t ys, int residua
     if (y0 < x1 && x0 < y1 && !(y0 == x0 && ys == c->cin))
       return ffail(TTSH_EINVAL, "output overlaps the input other than as its first channels");
   }
-  hipLaunchKernelGGL(k_to_bf16, dim3(nb(P * c->cin)), dim3(256), 0, c->s, x, c->xb, P * c->cin);
+  const long long nx = P * c->cin;
+  if (nx % 8 == 0 && ((uintptr_t)x & 15) == 0)
+    hipLaunchKernelGGL(k_to_bf16x8, dim3(nb(nx / 8)), dim3(256), 0, c->s, (const float4*)x, (uint4*)c->xb, nx / 8);
+  else
+    hipLaunchKernelGGL(k_to_bf16, dim3(nb(nx)), dim3(256), 0, c->s, x, c->xb, nx);
   const bool fuse = tail_fusable(c);
   const bool fuse_lift = fuse && c->cin <= kMaxLiftCin;
   int rc;

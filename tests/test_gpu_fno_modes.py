@@ -66,3 +66,21 @@ def test_refreshed_weights_are_the_parameters(gpu):
         assert np.array_equal(a.grads(), b.grads())
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("shift", [1, 2, 4])
+@pytest.mark.parametrize("cin", [2, 3])
+def test_input_alignment_does_not_matter(gpu, cin, shift):
+    """The input at any 4-byte alignment gives the bits of a 16-byte aligned one."""
+    import torch
+    from paper_2304_03306_amd import fno as F
+    print("[case] input alignment", cin, shift, flush=True)
+    net = F.FNO(width=32, modes=4, layers=1, cin=cin, H=16, W=16, max_batch=3, seed=2)
+    n = 3 * 16 * 16 * cin
+    buf = torch.randn(n + 8, device="cuda", generator=torch.Generator(device="cuda").manual_seed(4))
+    y = [torch.empty(3, 16, 16, 2, device="cuda") for _ in range(2)]
+    net.forward(buf[shift:shift + n].view(3, 16, 16, cin), y[0])
+    net.forward(buf[shift:shift + n].clone().view(3, 16, 16, cin), y[1])
+    torch.cuda.synchronize()
+    assert torch.equal(y[0], y[1])
+    net.close()
