@@ -24,8 +24,10 @@ struct Readout {
   static constexpr int NP = Padded<N>::value;
   // a wavefront per workgroup for the small sizes, and enough workgroups to
   // spread one field over the chip for the others
-  static constexpr int CPB = N <= 256 ? 512 / N : N <= 1024 ? 2 : 1;  // columns per workgroup
-  static constexpr int RPB = N <= 1024 ? 4 : N == 2048 ? 2 : 1;       // rows per workgroup
+  static constexpr int CPB = N <= 256 ? 512 / N : N <= 1024 ? 2 : 1;                        // columns per workgroup
+  static constexpr int RPB = N <= 128 ? 512 / N : N <= 1024 ? 4 : N == 2048 ? 2 : 1;  // rows per workgroup
+  // the kernels' reductions exchange values between all 64 lanes of a wavefront
+  static_assert(CPB * TT % 64 == 0 && RPB * TT % 64 == 0, "whole wavefronts");
   // LDS regions of a column's transforms: all of an 8192-point column's LDS
   // goes to one region
   static constexpr int SLOTS = N <= 4096 ? 2 : 1;

@@ -108,3 +108,31 @@ def test_projection(gpu, N, B, ch, shift):
         assert abs(nrm[b, 0] / (ref ** 2).sum() - 1) < 1e-12
         assert abs(nrm[b, 1] / (w ** 2).sum() - 1) < 1e-12
     s.close()
+
+
+@pytest.mark.parametrize("prec", [64, 32])
+@pytest.mark.parametrize("N", [64, 128, 256, 512])
+def test_an_empty_region_gives_nan(gpu, N, prec):
+    """Psi_2 where one region, left or right, or both hold no node (half-planes
+    beside the box, disks between the nodes or off the grid), and a number
+    where a region holds a single node."""
+    L = 0.3 * N
+    dx = L / N
+    print("[case] empty region", N, prec, flush=True)
+    s = gpu.Solver([N], [L], O.workload_params(), prec)
+    s.set_field(0, W.uniform_field(N + 5, N, 0.5, prec))
+    for cx in (-0.6 * L, 0.6 * L):
+        psi, psi2 = s.order(0, (cx, 0.0))
+        assert np.isfinite(psi) and np.isnan(psi2)
+    xn, yn = 3 * dx, -5 * dx  # a node
+    assert np.isnan(s.order_dumbbell(0, 0.5 * dx, (xn - 0.25 * dx, yn)))  # only the right disk has it
+    assert np.isnan(s.order_dumbbell(0, 0.5 * dx, (xn + 0.25 * dx, yn)))  # only the left one
+    assert np.isnan(s.order_dumbbell(0, 0.5 * dx, (xn - 0.25 * dx, yn + 0.5 * dx)))  # neither
+    assert np.isnan(s.order_dumbbell(0, 0.2 * L, (-0.55 * L, 0.0)))  # the left one off the grid
+    assert np.isnan(s.order_dumbbell(0, 0.2 * L, (0.52 * L, 0.0)))  # the right one
+    assert np.isnan(s.order_dumbbell(0, 0.2 * L, (0.0, 2.0 * L)))  # both
+    v, w = s.field(0, omega=True)
+    i, j = N // 2 - 5, N // 2 + 3
+    a, b = w[i, j], w[i, j + 1]  # one node in each disk
+    assert abs(s.order_dumbbell(0, dx, (xn + 0.5 * dx, yn)) - abs(a + b) / (abs(a) + abs(b))) < 1e-11
+    s.close()
