@@ -78,7 +78,7 @@ static_assert(TTSH_FFT_SLOTS >= 2, "the slot rotation needs at least two slots")
 // LDS regions of Padded<N> entries that NF transforms use during an exchange.
 // A one-wavefront tile (wave) needs a single one: its LDS accesses execute in
 // issue order, so a transform may overwrite the region as soon as the gather
-// of the one before has been issued.
+// of the one before has been issued (lds_sync keeps the compiler to that order).
 __host__ __device__ constexpr int fft_slots(int nf, bool wave = false) {
   return wave ? 1 : nf < TTSH_FFT_SLOTS ? nf : TTSH_FFT_SLOTS;
 }
@@ -260,10 +260,10 @@ struct Factors {
 // Orders the LDS accesses between the stages of a transform group.  With
 // WAVE, the group's workgroup is a single wavefront: the LDS unit executes one
 // wavefront's instructions in issue order, so a store is seen by every later
-// load of the same wavefront without a barrier or a wait for the store to
-// complete; a wavefront-scope fence (which emits no instruction) keeps the
-// compiler from moving the loads above the stores.  Otherwise a workgroup
-// barrier.
+// load of the same wavefront, and a load is not overtaken by a later store,
+// without a barrier or a wait for either to complete; a wavefront-scope fence
+// (which emits no instruction) keeps the compiler from moving the one across
+// the other.  Otherwise a workgroup barrier.
 template <bool WAVE>
 __device__ __forceinline__ void lds_sync() {
   if constexpr (WAVE) {
@@ -337,10 +337,12 @@ struct FftStage {
       lds_sync<WAVE>();
       FftStage<N, DIR, NF, P * R, T, SCH, WAVE, SN>::run(v, lds, t, tw);
     } else {
-      // transform f uses slot f % NS; the barrier after writing f also orders
-      // every read of f - NS (issued before it) ahead of the reuse of its slot
+      // transform f uses slot f % NS; with several slots the barrier after
+      // writing f also orders every read of f - NS (issued before it) ahead of
+      // the reuse of its slot, with one the reads of f - 1 need their own
 #pragma unroll
       for (int f = 0; f < NF; ++f) {
+        if (NS == 1 && f > 0) lds_sync<WAVE>();
         butterflies(v, f, lds + (f % NS) * NP, t, w);
         lds_sync<WAVE>();
         gather(v, f, lds + (f % NS) * NP, t);
