@@ -25,6 +25,8 @@
 // workgroups); threads that carry no useful data just transform zeros.
 #pragma once
 
+#include <cmath>
+
 #include "common.hpp"
 
 namespace ttsh {
@@ -137,24 +139,45 @@ struct Dft<8, DIR, T> {
 
 // ---- radix-R DFTs of twiddled inputs: sum_r u[r] w^r W_R^(r q) with
 // w = e^{DIR 2 pi i j / N} ------------------------------------------------------
-// As log2 R levels of radix-2 butterflies (a + w b, a - w b), each six fused
-// multiply-adds (the difference is 2 a - (a + w b)): 72 for R = 8 against 80
-// instructions for the products followed by the untwiddled DFT, and four
-// factors to load (w^4, w^2, w, w W8; those turned by i are the same numbers)
-// against seven.  With the shared LDS addresses above, a 512-point row tile
-// falls from 1552 to 1425 vector instructions and every 8192-point kernel
-// fits its 128 registers (69 to 110 were spilled).  The relative error of a
-// 100-step FP32 run against FP64 stays at 1e-7 (1.6e-7 before and after on a
-// 512^2 circle; 0.67e-7 -> 0.81e-7 after ten steps at 8192^2).
+// As log2 R levels of radix-2 butterflies (a + w b, a - w b) with the factor
+// w = c + i s held as (c, s/c): b + i (s/c) b takes two fused multiply-adds,
+// and a +- c times that four.  Radix 8 so takes 72 against the 80 instructions
+// of the products followed by the untwiddled DFT, and four factors to load
+// (w^4, w^2, w, w W8; those turned by i are the same numbers) against seven.
+// Every output goes through two roundings per level, the first of them of the
+// size of w b alone: the FP32 error of a transform of 64 to 8192 points is 0.96
+// to 0.99 of that of the products (forming a - w b as 2 a - (a + w b), also six
+// instructions, hands the sum's rounding on to the difference: 1.10 to 1.14).
 template <class T>
-__device__ __forceinline__ void bfly(C2<T>& a, C2<T>& b, T c, T s) {  // w = c + i s
-  const T x = fma(c, b.x, fma(-s, b.y, a.x)), y = fma(c, b.y, fma(s, b.x, a.y));
-  b = mk(fma((T)2, a.x, -x), fma((T)2, a.y, -y));
-  a = mk(x, y);
+__device__ __forceinline__ void bfly(C2<T>& a, C2<T>& b, C2<T> w) {
+  const T x = fma(-w.y, b.y, b.x), y = fma(w.y, b.x, b.y);
+  b = mk(fma(-w.x, x, a.x), fma(-w.x, y, a.y));
+  a = mk(fma(w.x, x, a.x), fma(w.x, y, a.y));
+}
+// the same with the factor DIR i w
+template <int DIR, class T>
+__device__ __forceinline__ void bfly_i(C2<T>& a, C2<T>& b, C2<T> w) {
+  const T x = fma(-w.y, b.y, b.x), y = fma(w.y, b.x, b.y), c = DIR * w.x;
+  b = mk(fma(c, y, a.x), fma(-c, x, a.y));
+  a = mk(fma(-c, y, a.x), fma(c, x, a.y));
 }
 template <int DIR, class T>
 __device__ __forceinline__ C2<T> turn(C2<T> w) {  // tables hold the forward sign
   return DIR > 0 ? conj(w) : w;
+}
+
+// Entry j < N/2 of a factor table: e^{-2 pi i j / N} as (c, s/c), s/c taken
+// with the rounded c so that s = c (s/c) carries one rounding.  A quarter turn
+// has c = 0: 2^-30 (2^-60 in FP64) stands for it, at most 1/32 of the other
+// factors' rounding; a quarter turn of values above 3e29 (1e290) overflows.
+template <class T>
+C2<T> fft_factor(int j, int N) {
+  const double a = 2.0 * M_PI * (double)j / (double)N;
+  const T c = 4 * j == N ? std::ldexp((T)1, sizeof(T) == 8 ? -60 : -30) : (T)std::cos(a);
+  C2<T> w;
+  w.x = c;
+  w.y = (T)(-std::sin(a) / (double)c);
+  return w;
 }
 
 // The four factors a thread's butterflies of one stage take: those of its one
@@ -185,8 +208,7 @@ struct DftTw;  // run(u, factors, butterfly)
 template <int DIR, class T>
 struct DftTw<2, DIR, T> {
   __device__ static __forceinline__ void run(C2<T> (&u)[2], const C2<T> (&f)[4], int b) {
-    const C2<T> w = turn<DIR>(f[b]);
-    bfly(u[0], u[1], w.x, w.y);
+    bfly(u[0], u[1], turn<DIR>(f[b]));
   }
 };
 
@@ -194,10 +216,10 @@ template <int DIR, class T>
 struct DftTw<4, DIR, T> {
   __device__ static __forceinline__ void run(C2<T> (&u)[4], const C2<T> (&f)[4], int b) {
     const C2<T> w2 = turn<DIR>(f[2 * b]), w = turn<DIR>(f[2 * b + 1]);
-    bfly(u[0], u[2], w2.x, w2.y);  // even q, odd q
-    bfly(u[1], u[3], w2.x, w2.y);
-    bfly(u[0], u[1], w.x, w.y);                // q = 0, 2
-    bfly(u[2], u[3], -DIR * w.y, DIR * w.x);   // q = 1, 3
+    bfly(u[0], u[2], w2);  // even q, odd q
+    bfly(u[1], u[3], w2);
+    bfly(u[0], u[1], w);         // q = 0, 2
+    bfly_i<DIR>(u[2], u[3], w);  // q = 1, 3
     const C2<T> x = u[1];
     u[1] = u[2];
     u[2] = x;
@@ -209,16 +231,16 @@ struct DftTw<8, DIR, T> {
   __device__ static __forceinline__ void run(C2<T> (&u)[8], const C2<T> (&f)[4], int) {
     const C2<T> w4 = turn<DIR>(f[0]), w2 = turn<DIR>(f[1]), w = turn<DIR>(f[2]), w1 = turn<DIR>(f[3]);
 #pragma unroll
-    for (int a = 0; a < 4; ++a) bfly(u[a], u[a + 4], w4.x, w4.y);  // even q in 0..3, odd in 4..7
+    for (int a = 0; a < 4; ++a) bfly(u[a], u[a + 4], w4);  // even q in 0..3, odd in 4..7
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
-      bfly(u[a], u[a + 2], w2.x, w2.y);                  // q mod 4 = 0, 2
-      bfly(u[4 + a], u[6 + a], -DIR * w2.y, DIR * w2.x);  // q mod 4 = 1, 3
+      bfly(u[a], u[a + 2], w2);                // q mod 4 = 0, 2
+      bfly_i<DIR>(u[4 + a], u[6 + a], w2);  // q mod 4 = 1, 3
     }
-    bfly(u[0], u[1], w.x, w.y);                // q = 0, 4
-    bfly(u[2], u[3], -DIR * w.y, DIR * w.x);   // q = 2, 6
-    bfly(u[4], u[5], w1.x, w1.y);              // q = 1, 5
-    bfly(u[6], u[7], -DIR * w1.y, DIR * w1.x);  // q = 3, 7
+    bfly(u[0], u[1], w);          // q = 0, 4
+    bfly_i<DIR>(u[2], u[3], w);   // q = 2, 6
+    bfly(u[4], u[5], w1);         // q = 1, 5
+    bfly_i<DIR>(u[6], u[7], w1);  // q = 3, 7
     const C2<T> x1 = u[1], x3 = u[3], x6 = u[6];
     u[1] = u[4];
     u[4] = x1;
@@ -276,7 +298,8 @@ __device__ __forceinline__ void lds_sync() {
 
 // ---- one Stockham stage, recursing into the next ---------------------------
 // v[f][e] holds element t + e*TT of transform f.  `lds` points at this group's
-// fft_slots(NF) regions of Padded<N> entries each.  `tw[j]` = e^{-2 pi i j / N}.
+// fft_slots(NF) regions of Padded<N> entries each.  tw: the table
+// of fft_factor(j, N), or its entries of every stage (Factors).
 template <int N, int DIR, int NF, int P, class T, int SCH, bool WAVE, int S = 0>
 struct FftStage {
   static constexpr int E = kFftE;

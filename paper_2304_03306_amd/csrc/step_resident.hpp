@@ -43,7 +43,7 @@ struct Resident {
   // 1024 threads leave 128 registers each: the column's state stays in memory
   // (the L2) and the factors in LDS instead of being held in registers
   static constexpr bool TIGHT = NT > 512;
-  static constexpr size_t factors = TIGHT ? N * sizeof(C2<T>) : 0;
+  static constexpr size_t factors = TIGHT ? N / 2 * sizeof(C2<T>) : 0;
   static constexpr size_t bytes = region + tables + herm + factors + (NT / 64) * 2 * sizeof(double);
 };
 
@@ -61,7 +61,7 @@ template <int N, class T>
 struct ResidentFactors<N, T, true> {
   const C2<T>* f;
   __device__ __forceinline__ void init(const C2<T>* tw, C2<T>* lds, int, int tid) {
-    if (tid < N) lds[tid] = tw[tid];
+    if (tid < N / 2) lds[tid] = tw[tid];
     f = lds;
   }
   template <int DIR, int NF>

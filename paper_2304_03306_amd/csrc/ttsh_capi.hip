@@ -276,24 +276,16 @@ void drop_graph(ttsh_ctx* c) {
   c->rem_steps = 0;
 }
 
-int make_twiddles(int N, bool fp64, void** out) {
-  std::vector<double> w(2 * N);
-  for (int j = 0; j < N; ++j) {
-    const double a = 2.0 * M_PI * (double)j / (double)N;
-    w[2 * j] = std::cos(a);
-    w[2 * j + 1] = -std::sin(a);
-  }
-  if (fp64) {
-    HIPCHK(hipMalloc(out, sizeof(double) * 2 * N));
-    HIPCHK(hipMemcpy(*out, w.data(), sizeof(double) * 2 * N, hipMemcpyHostToDevice));
-  } else {
-    std::vector<float> f(2 * N);
-    for (int j = 0; j < 2 * N; ++j) f[j] = (float)w[j];
-    HIPCHK(hipMalloc(out, sizeof(float) * 2 * N));
-    HIPCHK(hipMemcpy(*out, f.data(), sizeof(float) * 2 * N, hipMemcpyHostToDevice));
-  }
+// the factor table of the transforms of length N (fft_factor)
+template <class T>
+int factor_table(int N, void** out) {
+  std::vector<C2<T>> w(N / 2);
+  for (int j = 0; j < N / 2; ++j) w[j] = fft_factor<T>(j, N);
+  HIPCHK(hipMalloc(out, w.size() * sizeof(C2<T>)));
+  HIPCHK(hipMemcpy(*out, w.data(), w.size() * sizeof(C2<T>), hipMemcpyHostToDevice));
   return TTSH_OK;
 }
+int make_twiddles(int N, bool fp64, void** out) { return fp64 ? factor_table<double>(N, out) : factor_table<float>(N, out); }
 
 int max_N(const ttsh_ctx* c) {
   int m = 0;

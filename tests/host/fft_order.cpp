@@ -19,11 +19,17 @@ static std::vector<C> table(int N) {
   return w;
 }
 
+static std::vector<C> factors(int N) {
+  std::vector<C> w(N / 2);
+  for (int j = 0; j < N / 2; ++j) w[j] = fft_factor<double>(j, N);
+  return w;
+}
+
 template <int N, int DIR, int NF, int SCH, bool WAVE, bool KEPT>
 void one(bool descending) {
   constexpr int TT = N / kFftE, G = WAVE ? 64 / TT : 1, NT = G * TT;
   constexpr int REG = fft_slots(NF, WAVE) * Padded<N, SCH>::value;
-  const std::vector<C> tw = table(N);
+  const std::vector<C> tw = factors(N), wave = table(N);
   std::mt19937_64 gen(7 * N + NF);
   std::uniform_real_distribution<double> U(-1, 1);
   std::vector<C> x((size_t)G * NF * N), y(x.size()), lds((size_t)G * REG);
@@ -48,7 +54,7 @@ void one(bool descending) {
     for (int m = 0; m < N; ++m) {
       C s = mk(0.0, 0.0);
       for (int n = 0; n < N; ++n) {
-        const C w = tw[(size_t)m * n % N];
+        const C w = wave[(size_t)m * n % N];
         s = s + cmul(x[(size_t)q * N + n], DIR > 0 ? conj(w) : w);
       }
       const C d = y[(size_t)q * N + m] - s;
