@@ -18,6 +18,7 @@
 #include "aux.hpp"
 #include "launch.hpp"
 #include "readout.hpp"
+#include "resident_rule.hpp"
 #include "step_multi.hpp"
 
 using namespace ttsh;
@@ -493,21 +494,18 @@ hipError_t launch_col(ttsh_ctx* c, const MultiArgs& m, int mode, hipStream_t s) 
   return hipSuccess;
 }
 
-// Whether the steps run in resident workgroups (step_resident.hpp): one-stage
-// schemes on contexts whose every grid fits one workgroup's LDS.  64 points:
-// always (a step takes 7.3 us for 1 to 256 FP32 instances against 12.2 to 19.6
-// with the two passes, 9.8 against 28.5 for 256 in FP64).  128 points, FP32
-// transforms: a step takes 18 us up to 256 instances (one per compute unit,
-// bound by its vector instructions) and then grows with their number, while
-// the two passes take 13.5 us for 16, 17.6 for 64 and 45 for 256; the lines
-// cross near 70, so from 96 on.
-constexpr int kResident128 = 96;
 constexpr int kResidentSteps = 500;  // longest launch
+// Whether the steps run in resident workgroups (step_resident.hpp): one-stage
+// schemes on contexts whose every grid fits one workgroup's LDS, where
+// resident_pays says that it is the faster.
 bool resident(const ttsh_ctx* c) {
   if (c->p.scheme > TTSH_IMEX) return false;
-  for (auto& k : c->cls)
-    if (!(k.N == 64 || (k.N == 128 && c->prec != 64 && (int)k.ids.size() >= kResident128))) return false;
-  return true;
+  int n64 = 0, n128 = 0;
+  for (auto& k : c->cls) {
+    if (k.N != 64 && (k.N != 128 || c->prec == 64)) return false;
+    (k.N == 64 ? n64 : n128) = (int)k.ids.size();
+  }
+  return resident_pays(n64, n128, c->gw != 0);
 }
 
 hipError_t launch_resident(ttsh_ctx* c, const MultiArgs& m, int steps, hipStream_t s) {
