@@ -105,12 +105,20 @@ typedef struct {
 /* Options for ttsh_set_option. */
 enum {
   TTSH_OPT_GRAPH_STEPS = 1, /* steps captured per HIP graph (0 = no graph); default 50 */
-  TTSH_OPT_BLOCK = 2,       /* workgroup size of the step kernels: 64, 128 or 256
-                               (8 x size >= largest N), 0 = chosen from the batch */
+  TTSH_OPT_BLOCK = 2,       /* workgroup size of the row and column passes: 64, 128 or
+                               256 (8 x size >= largest N), 0 = chosen from the batch.
+                               Contexts of 64-point grids, and of enough 128-point ones
+                               (FP32 transforms), with a one-stage scheme step without
+                               these passes: a workgroup holds an instance through many
+                               steps ("resident").  There this option, TTSH_OPT_SPLIT
+                               and the sizes, splits and schedules of ttsh_set_tuning
+                               are checked and kept but change nothing. */
   TTSH_OPT_GUARD = 4,       /* 1: ttsh_sync checks the state for NaN/Inf; default 1 */
   TTSH_OPT_SPLIT = 8,       /* bit 0: row pass, bit 1: column pass launched once per grid
                                size (kernels compiled for that size) instead of once for
-                               all sizes; default 0 */
+                               all sizes; default 0.  A context of one grid size takes
+                               that size's kernels either way, unless another transform
+                               schedule was set (ttsh_set_tuning, ttsh_tune) */
   TTSH_OPT_GUARD_EVERY = 16,/* with the guard on: steps between the NaN/Inf checks that
                                ttsh_step queues (part of the captured graphs; one launch
                                per grid size over all its instances, flags kept on the
@@ -355,7 +363,9 @@ int ttsh_sync(ttsh_ctx* ctx);
  * launch durations in microseconds: out[0] = row pass, out[1] = column pass
  * (each launch covers every instance).  The row pass always reads the same
  * fields; the column pass re-applies its update with the same forcing, so
- * the state changes: save it first if it matters.  Synchronous.            */
+ * the state changes: save it first if it matters.  These are the two passes
+ * also where ttsh_step does without them (resident contexts, see
+ * TTSH_OPT_BLOCK): its time is that of ttsh_step there.  Synchronous.       */
 int ttsh_pass_times(ttsh_ctx* ctx, int64_t nsteps, double* out);
 
 /* Autotuner: for each of the two passes of a step, independently, time
@@ -364,7 +374,8 @@ int ttsh_pass_times(ttsh_ctx* ctx, int64_t nsteps, double* out);
  * keep the fastest (each candidate's faster round):
  *   workgroup size 64, 128 or 256 (the rows or columns per tile follow:
  *   size / (N/8) for a grid of N points);
- *   one launch for all grid sizes, or one launch per grid size;
+ *   one launch for all grid sizes, or one launch per grid size (contexts of
+ *   several sizes);
  *   with one launch for all sizes in the FP32 arithmetic, the transform
  *   schedule: the LDS padding (one slot per 8, 16 or 32 entries) and, for
  *   grids that are not a power of 8, whether the leftover radix (2 or 4)
@@ -373,7 +384,9 @@ int ttsh_pass_times(ttsh_ctx* ctx, int64_t nsteps, double* out);
  * Then whole steps (replayed as ttsh_step runs them, nsteps per candidate,
  * two rounds) decide between the column-pass sizes (each with its fastest
  * split and schedule) and between one and two concurrent instance groups
- * (TTSH_OPT_GROUPS), the row pass keeping its choice.
+ * (TTSH_OPT_GROUPS), the row pass keeping its choice.  Resident contexts (see
+ * TTSH_OPT_BLOCK) step without the passes: whole steps decide the number of
+ * groups, and the rest of the configuration stays as it was.
  * The state the context had before the call is restored.  cfg_out (7 ints,
  * may be NULL): row-pass size, column-pass size, row split (0/1), column
  * split (0/1), row schedule, column schedule, groups (the layout of

@@ -1752,7 +1752,12 @@ int ttsh_tune(ttsh_ctx* c, int64_t nsteps, int* cfg_out, double* us_out) {
     double row, col;
   };
   std::vector<Cand> cands;
-  for (int split = must_split(c) ? 1 : 0; split < 2; ++split)
+  // resident steps launch neither pass: only the number of groups is timed, and
+  // the passes' configuration stays.  One launch per size is a candidate of its
+  // own only where there are several sizes (one_size).
+  const bool res = resident(c);
+  const int splits = must_split(c) || c->cls.size() > 1 ? 2 : 1;
+  for (int split = must_split(c) ? 1 : 0; split < splits && !res; ++split)
     for (int bs : {64, 128, 256}) {
       if (!bs_valid(c, bs)) continue;
       const int nsch = sched_usable(c, split) ? 1 + kNumSchedVariants : 1;
@@ -1773,6 +1778,11 @@ int ttsh_tune(ttsh_ctx* c, int64_t nsteps, int* cfg_out, double* us_out) {
     if (!best_row[0] || k.row < row_us) { best_row[0] = k.bs; best_row[1] = k.split; best_row[2] = k.sch; row_us = k.row; }
     if (!best_col[0] || k.col < col_us) { best_col[0] = k.bs; best_col[1] = k.split; best_col[2] = k.sch; col_us = k.col; }
   }
+  if (res)
+    for (int q = 0; q < 3; ++q) {
+      best_row[q] = keep[2 * q];
+      best_col[q] = keep[2 * q + 1];
+    }
   // Whole steps decide the column workgroup size and the number of
   // concurrent groups: with two groups the row pass of one runs beside the
   // column pass of the other, and the column size that is fastest alone need
@@ -1800,6 +1810,8 @@ int ttsh_tune(ttsh_ctx* c, int64_t nsteps, int* cfg_out, double* us_out) {
       if (!b) continue;
       for (int G = 1; G <= std::min(kMaxGroups, c->n_inst); ++G) whole.push_back({bs, b->split, b->sch, G, 1e30});
     }
+    if (res)
+      for (int G = 1; G <= std::min(kMaxGroups, c->n_inst); ++G) whole.push_back({keep[1], keep[3], keep[5], G, 1e30});
     hipEvent_t w0 = nullptr, w1 = nullptr;
     if (hipEventCreate(&w0) != hipSuccess || hipEventCreate(&w1) != hipSuccess)
       rc = fail(TTSH_EHIP, "event creation failed");
