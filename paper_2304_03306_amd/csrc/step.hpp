@@ -205,21 +205,23 @@ __device__ __forceinline__ size_t mix_idx(int f, int m, int y) {
   return (size_t)f * Geo<N>::MP4 * N + (size_t)(m >> 2) * (4 * N) + 4 * y + (m & 3);
 }
 
-// The same pointer, opaque to the compiler if FRESH: the factors behind it are
-// then read again instead of being kept in registers from one transform to
-// the next.  Of the sizes whose workgroups hold several wavefronts per
-// transform the largest lose more to the registers (at 8192 points they would
-// spill; at 2048 the row pass takes 160 us with the kept factors and 139 us
-// without, six paper-preset instances) than the second reads cost; up to 1024
-// points keeping them is the faster (radius sweep 69.7 against 71.5 us a step).
-constexpr int kReloadN = 2048;
-
 // A pass's factors: up to kPreloadN points loaded before its data, so that
 // their latency runs beside the data's instead of in each stage's serial
 // chain (a 512^2 circle alone 16.1 -> 15.7 us a step, the radius sweep 62.8 ->
-// 60.9, ten 512^2 FP64 instances 44.7 -> 42.2); beyond that the three or four
-// twiddled stages' factors would cost the registers that kReloadN frees.
+// 60.9, ten 512^2 FP64 instances 44.7 -> 42.2).  Beyond that the factors of
+// three or four twiddled stages cost more as registers than reading them
+// costs, also for the pass's second transform (at 8192 points they would
+// spill; at 2048 the row pass of six paper-preset instances takes 160 us with
+// the factors kept from the first transform and 139 us read again).
 constexpr int kPreloadN = 1024;
+// the same pointer, opaque to the compiler: what was read through the other is
+// not kept for it
+template <class T>
+__device__ __forceinline__ const C2<T>* reload(const C2<T>* tw) {
+  auto g = (const __attribute__((address_space(1))) C2<T>*)tw;
+  asm volatile("" : "+s"(g));
+  return (const C2<T>*)g;
+}
 template <int N, class T, int SCH>
 struct StepFactors {
   static constexpr bool PRE = N <= kPreloadN;
@@ -233,18 +235,9 @@ struct StepFactors {
     if constexpr (PRE)
       fft<N, DIR, NF, SCH, WAVE>(v, lds, t, f);
     else
-      fft<N, DIR, NF, SCH, WAVE>(v, lds, t, reload<(SECOND && N >= kReloadN)>(tw));
+      fft<N, DIR, NF, SCH, WAVE>(v, lds, t, SECOND ? reload(tw) : tw);
   }
 };
-template <bool FRESH, class T>
-__device__ __forceinline__ const C2<T>* reload(const C2<T>* tw) {
-  if constexpr (FRESH) {
-    auto g = (const __attribute__((address_space(1))) C2<T>*)tw;
-    asm volatile("" : "+s"(g));
-    return (const C2<T>*)g;
-  }
-  return tw;
-}
 
 // z = p + i q
 template <class T>
