@@ -77,3 +77,57 @@ def test_resident_guard_sees_a_non_finite_state(gpu):
     with pytest.raises(gpu.TTSHError):
         s.sync()
     s.close()
+
+
+@pytest.mark.parametrize("preset,n128", [("workload", 130), ("paper", 170)])
+@pytest.mark.parametrize("prec", [32, 96])
+def test_two_resident_sizes_match_two_passes(gpu, preset, n128, prec):
+    """64- and 128-point instances in one context, each size in a launch of its
+    own, with one and two groups."""
+    import torch
+    print("[case] resident mixed", preset, n128, prec, flush=True)
+    p = W.paper_coefficients() if preset == "paper" else W.workload_coefficients()
+
+    def run(with_large, groups):
+        Ns = [64] * 3 + [128] * n128 + ([256] if with_large else [])
+        s = gpu.Solver(Ns, [0.4 * m for m in Ns], p, prec)
+        if groups > 1:
+            s.option(gpu.TTSH_OPT_GROUPS, groups)
+        for q, N in enumerate(Ns):
+            s.mask_tanh(q, [(0.0, 0.0)], [0.125 * N], 0.5)
+            gen = torch.Generator(device="cuda").manual_seed(31 + q)
+            v = torch.rand(2, N, N, generator=gen, device="cuda", dtype=torch.float64) - 0.5
+            s.set_field(q, v.float().double())
+        s.step(60)
+        s.sync()
+        out = [s.state(q) for q in (0, 2, 3, 4 + n128 // 2, n128 + 2)]
+        s.close()
+        return out
+
+    ref = run(True, 1)
+    for got in (run(False, 1), run(False, 2)):
+        for x, y in zip(got, ref):
+            assert np.linalg.norm(x - y) < 1e-6 * np.linalg.norm(y)
+
+
+@pytest.mark.parametrize("graph", [0, 50])
+@pytest.mark.parametrize("every,caught", [(7, True), (20, True), (21, False), (0, False)])
+def test_resident_guard_looks_at_its_interval(gpu, every, caught, graph):
+    """A state that overflows within a run of 20 steps and is replaced before
+    the sync: only a check queued within the run can have seen it."""
+    import dataclasses
+    print("[case] resident guard interval", every, graph, flush=True)
+    p = dataclasses.replace(W.workload_coefficients(), gamma_v=1e6)
+    s = gpu.Solver([64, 64], [25.6, 25.6], p, 32)
+    s.option(gpu.TTSH_OPT_GRAPH_STEPS, graph)
+    s.option(gpu.TTSH_OPT_GUARD_EVERY, every)
+    s.mask_tanh(0, [(0.0, 0.0)], [8.0], 0.5)  # the other instance has no wall
+    for q in range(2):
+        s.set_field(q, W.uniform_field(1, 64, 0.5, 32))
+    s.step(20)
+    s.set_field(0, W.uniform_field(1, 64, 0.5, 32))
+    if caught:
+        with pytest.raises(gpu.TTSHError, match="instance 0"):
+            s.sync()
+    s.sync()  # clean, or cleared by the report
+    s.close()
