@@ -136,3 +136,101 @@ def test_an_empty_region_gives_nan(gpu, N, prec):
     a, b = w[i, j], w[i, j + 1]  # one node in each disk
     assert abs(s.order_dumbbell(0, dx, (xn + 0.5 * dx, yn)) - abs(a + b) / (abs(a) + abs(b))) < 1e-11
     s.close()
+
+
+def _plane_waves(s, N, L):
+    """Sets a divergence-free state of a few modes (the mean, the m_x = 0 column,
+    both axes' ends, the disk's rim, the lowest and some random ones) and
+    returns its velocity and vorticity as sums of plane waves in FP64."""
+    M = N // 4
+    rng = np.random.default_rng(N)
+    modes = [(0, M), (0, 1), (M, 0), (1, 0), (1, 1), (1, -1), (3 * M // 5, 4 * M // 5), (4 * M // 5, -(3 * M // 5))]
+    while len(modes) < 16:
+        m = (int(rng.integers(1, M)), int(rng.integers(-M, M)))
+        if m[0] ** 2 + m[1] ** 2 <= M * M and m not in modes:
+            modes.append(m)
+    c = np.zeros((2, 2 * M + 1, M + 1), dtype=np.complex128)
+    c[:, M, 0] = N * rng.standard_normal(2)  # the mean flow
+    for mx, my in modes:
+        a = N * complex(*rng.standard_normal(2)) / np.hypot(mx, my)
+        c[:, my + M, mx] = -my * a, mx * a
+        if mx == 0:
+            c[:, M - my, 0] = np.conj(c[:, my + M, 0])
+    s.set_state(0, c)
+    c = s.state(0)
+    dk = 2 * np.pi / L
+    i = np.arange(N)
+    left, right = [], []  # the fields are left.T @ right, per component
+    for my, mx in np.argwhere(np.abs(c).max(0) > 0):
+        my -= M
+        ex = 2 * np.pi * ((mx * i) % N) / N
+        ey = 2 * np.pi * ((my * i) % N) / N
+        a = (1.0 if mx == 0 else 2.0) / N * c[:, my + M, mx]
+        a = [a[0], a[1], 1j * dk * (mx * a[1] - my * a[0])]
+        left.append([[(q * np.exp(1j * ey)).real, -(q * np.exp(1j * ey)).imag] for q in a])
+        right += [np.cos(ex), np.sin(ex)]
+    right = np.array(right)
+    left = np.array(left).transpose(1, 0, 2, 3).reshape(3, -1, N)
+    v = np.stack([left[q].T @ right for q in (0, 1)])
+    return v, left[2].T @ right
+
+
+@pytest.mark.parametrize("N,prec", [(2048, 64), (4096, 64), (8192, 96)])
+def test_production_sizes(gpu, N, prec):
+    """Velocity, vorticity, float pixels of either alignment and both order
+    parameters where a workgroup has one row or one column, or one LDS region."""
+    import torch
+    L = 0.005 * N
+    print("[case] production size", N, prec, flush=True)
+    s = gpu.Solver([N], [L], O.workload_params(), prec)
+    vr, wr = _plane_waves(s, N, L)
+    v, w = s.field(0, omega=True)
+    big = np.abs(vr).max()
+    assert np.abs(v - vr).max() < 1e-12 * big
+    assert np.abs(w - wr).max() < 1e-12 * np.abs(wr).max()
+    for stride, shift in ((2, 0), (3, 1)):
+        buf = torch.full((N * N * stride + shift,), 7.0, dtype=torch.float32, device="cuda")
+        s.field_coarse(0, N, buf[shift:], stride)
+        got = buf[shift:].view(N, N, stride)
+        for c in range(2):
+            assert np.abs(got[:, :, c].cpu().numpy() - vr[c]).max() < 1.2e-7 * big
+        assert (got[:, :, 2:] == 7.0).all() and (buf[:shift] == 7.0).all()
+        del buf, got
+    cen, D = (0.03 * L, -0.02 * L), 0.4 * L
+    psi, psi2 = s.order(0, cen)
+    assert abs(psi - O.vortex_order(v, L, cen)) < 1e-11
+    assert abs(psi2 - O.vortex_order2(w, L, cen[0])) < 1e-11
+    assert abs(s.order_dumbbell(0, D, cen) - O.vortex_order2(w, L, cen[0], D=D, center_y=cen[1])) < 1e-11
+    s.close()
+
+
+@pytest.mark.parametrize("N,B,ch,shift", [(2048, 2, 3, 0), (4096, 1, 2, 1), (8192, 1, 2, 0)])
+def test_projection_of_production_sizes(gpu, N, B, ch, shift):
+    """As test_projection, with the reference's transforms by torch in FP64."""
+    import torch
+    print("[case] project", N, B, ch, shift, flush=True)
+    buf = torch.zeros(B * N * N * ch + shift, dtype=torch.float32, device="cuda")
+    buf[shift:] = torch.randn(B * N * N * ch, device="cuda", generator=torch.Generator(device="cuda").manual_seed(N))
+    x = buf[shift:].view(B, N, N, ch).clone()
+    s = gpu.Solver([64], [20.0], O.workload_params(), 32)
+    nrm = s.project_coarse(N, buf[shift:], ch, B, norms=True)
+    got = buf[shift:].view(B, N, N, ch)
+    assert torch.equal(got[..., 2:], x[..., 2:])
+    mx = torch.arange(N // 2 + 1, device="cuda", dtype=torch.float64)[None, :]
+    my = torch.fft.fftfreq(N, 1.0 / N, device="cuda", dtype=torch.float64)[:, None]
+    m2 = mx ** 2 + my ** 2
+    keep = m2 <= (N // 4) ** 2
+    for b in range(B):
+        h = [torch.fft.rfft2(x[b, :, :, c].double()) * keep for c in range(2)]
+        d = (mx * h[0] + my * h[1]) / m2.clamp_min(1.0)
+        h = [h[0] - mx * d, h[1] - my * d]
+        del d
+        w = torch.fft.irfft2(1j * (mx * h[1] - my * h[0]), s=(N, N))
+        assert abs(nrm[b, 1] / (w ** 2).sum().item() - 1) < 1e-12
+        del w
+        v = [torch.fft.irfft2(q, s=(N, N)) for q in h]
+        big = max(q.abs().max().item() for q in v)
+        for c in range(2):
+            assert (got[b, :, :, c].double() - v[c]).abs().max().item() < 1.2e-7 * big
+        assert abs(nrm[b, 0] / sum((q ** 2).sum().item() for q in v) - 1) < 1e-12
+    s.close()
