@@ -84,3 +84,45 @@ def test_input_alignment_does_not_matter(gpu, cin, shift):
     torch.cuda.synchronize()
     assert torch.equal(y[0], y[1])
     net.close()
+
+
+@pytest.mark.parametrize("modes,size", [(3, 32), (8, 32), (16, 64)])
+@pytest.mark.parametrize("batch", [1, 63, 64, 65, 130])
+def test_mode_gradients_are_the_sums_of_the_captured_modes(gpu, modes, size, batch):
+    """The per-mode products of the BF16 modes that the kernel read, summed in
+    FP64: 2 batch terms added in FP32 with at most 2^-23 of the partial sum lost
+    at each, so (2 batch + 4) 2^-23 of the sum of absolute terms."""
+    import torch
+    from paper_2304_03306_amd import fno as F
+    print("[case] mode gradient sums", modes, size, batch, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(100 + batch)
+    x = torch.randn(batch, size, size, 3, device="cuda", generator=gen)
+    t = torch.randn(batch, size, size, 2, device="cuda", generator=gen)
+    y = torch.empty_like(t)
+    m, C = modes, 32
+    net = F.FNO(width=C, modes=m, layers=2, H=size, W=size, max_batch=batch, seed=6)
+    net.set_option(F.FNO_OPT_CAPTURE, 1)
+    net.forward(x, y, train=True)
+    net.loss(y, t)
+    net.backward(batch)
+    g = net.grads().astype(np.float64)
+    nG = m * 4 * m * batch * C
+    nR = 2 * m * m * C * C
+    o = 3 * C + C
+    for l in range(2):
+        f, d = (net.capture(w, l, nG).reshape(m, 4 * m, batch, C) for w in (F.FNO_CAP_G, F.FNO_CAP_GG))
+        f, d = ([a[:, :2 * m], a[:, 2 * m:]] for a in (f, d))
+
+        def products(u, v):  # [kx][q][c][o] -> [q][kx][c][o]
+            return np.matmul(u.swapaxes(2, 3), v).swapaxes(0, 1)
+
+        for ref, size_ in ((products(f[0], d[0]) + products(f[1], d[1]),
+                            products(abs(f[0]), abs(d[0])) + products(abs(f[1]), abs(d[1]))),
+                           (products(f[0], d[1]) - products(f[1], d[0]),
+                            products(abs(f[0]), abs(d[1])) + products(abs(f[1]), abs(d[0])))):
+            got = g[o:o + nR].reshape(2 * m, m, C, C)
+            assert (size_ > 0).any()
+            assert (np.abs(got - ref) <= (2 * batch + 4) * 2.0 ** -23 * size_ + 1e-30).all()
+            o += nR
+        o += C * C + C
+    net.close()
