@@ -1,24 +1,26 @@
 // Workgroup-level Stockham FFT staged through LDS, for gfx950.
 //
-// One transform of length N (64..2048, a power of two) is carried by TT = N/8
+// One transform of length N (64..8192, a power of two) is carried by TT = N/8
 // threads of a workgroup; thread t holds the 8 elements t + e*TT (e = 0..7)
-// in registers.  Each stage of radix R (8, or a final 4 or 2) reads its
-// butterfly inputs x[i + r*N/R] from exactly those registers, multiplies by
-// the twiddles w^(r*k) (k = i mod P, P the product of the earlier radices),
-// does the radix-R DFT and scatters the outputs to y[(i-k)R + k + rP]
-// (Stockham autosort, decimation in time; Van Loan, Computational Frameworks
-// for the FFT, ch. 1.7).  Because the input stride N/R is the same in every
-// stage, the scatter is followed by a gather of t + e*TT, and in the last stage
-// (P = N/R) the scatter target is t + e*TT itself, so the output lands in the
-// registers that held the input, in natural order.  A transform therefore
-// costs (#stages - 1) LDS round trips and needs no bit reversal.
+// in registers.  Each stage of radix R (8, and one 4 or 2) reads its butterfly
+// inputs x[i + r*N/R] from exactly those registers, takes the radix-R DFT of
+// their products with w^(r*k) (k = i mod P, P the product of the earlier
+// radices; w^(r*k) inside the DFT's own butterflies, see DftTw) and scatters
+// the outputs to y[(i-k)R + k + rP] (Stockham autosort, decimation in time; Van
+// Loan, Computational Frameworks for the FFT, ch. 1.7).  Because the input
+// stride N/R is the same in every stage, the scatter is followed by a gather of
+// t + e*TT, and in the last stage (P = N/R) the scatter target is t + e*TT
+// itself, so the output lands in the registers that held the input, in natural
+// order.  A transform therefore costs (#stages - 1) LDS round trips and needs
+// no bit reversal.
 //
 // NF independent transforms that share the same threads are processed
 // together.  At most TTSH_FFT_SLOTS of them occupy LDS at a time: with as many
 // slots as transforms one barrier pair per stage serves all of them; with
 // fewer, the transforms take turns in the slots (one more barrier per extra
 // transform and stage), which shrinks the LDS footprint of a transform group
-// and lets more waves stay resident on a CU.
+// and lets more waves stay resident on a CU.  One-wavefront workgroups, whose
+// barriers cost nothing, use a single slot.
 //
 // All threads of the workgroup must call these functions (they contain
 // workgroup barriers, or wavefront-scope ordering for one-wavefront

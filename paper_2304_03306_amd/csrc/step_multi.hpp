@@ -165,8 +165,13 @@ __global__ void __launch_bounds__(BS) col_multi(MultiArgs a) {
 // Grids of 2048 points are served only here (their tiles would raise the
 // register budget of the multi-size kernels for every other size).
 // Wavefronts per SIMD the compiler has to make room for: two of 4096 points'
-// 512-thread FP32 workgroups share a compute unit with 128 registers each
-// (the column pass with the vorticity source would take 131 and run alone).
+// 512-thread FP32 workgroups share a compute unit with 128 registers each.  The
+// column pass with the vorticity source would take 131 and more and run alone;
+// held to 128 it spills up to 10 of them and is still the faster in every mode:
+// 93 against 126 us for one paper-preset instance and 198 against 267 for two,
+// 108 against 122 and 229 against 273 with the FP64 state (ETDRK4 steps 923
+// against 964 us, 948 against 989).  Without the source the bound changes
+// nothing (within 1 %).
 template <int N, class T>
 constexpr int min_waves() {
   return N == 4096 && sizeof(T) == 4 ? 4 : 1;

@@ -10,10 +10,12 @@
 // barrier.  One LDS region serves in turn as X [3][M+1][N], the row
 // transforms' exchange, Y [2 or 3][M+1][N] and the columns' exchange.
 //
-// Bound by one compute unit's vector instructions and their latency: a step
-// takes 7.3 us at 64^2 (9.2 us in FP64) against 12.2 (14.4) for two launches
-// with one instance, and at 128^2 18 to 20 us for up to 256 instances against
-// 45 us for 256 (FP32, workload coefficients).
+// Bound by latency in the one compute unit that an instance has: at 64^2 a
+// wavefront per SIMD (FP64: about a quarter of the unit's rate) takes 7.4 us a
+// step (9.2 us in FP64) against 12.2 (14.1) for two launches with one instance;
+// at 128^2 four per SIMD take 19 to 21 us for up to 256 instances, 23 to 28 with
+// the vorticity source, against 38 and 43 us for 256 (FP32; where the lines
+// cross: resident_rule.hpp).
 #pragma once
 
 #include "step_multi.hpp"

@@ -727,9 +727,13 @@ int ensure_groups(ttsh_ctx* c) {
     return fail(TTSH_EHIP, "event creation failed");
   for (int g = 0; g < c->groups; ++g) {
     // The runtime deals streams out to a few hardware queues, and two streams
-    // on one queue do not overlap (radius sweep: 89 us per step instead of 61).
+    // on one queue do not overlap (radius sweep: 89 us per step instead of 59).
     // Two streams made one right after the other landed on the same queue in
-    // a process's first context; with a stream made between them they did not.
+    // a process's first context; with a stream made between them they did not,
+    // there and in each of the seven contexts made after it, with the earlier
+    // ones closed or kept and after up to three other streams (58 to 60 us in
+    // all forty).  Where the runtime deals otherwise, the groups still give the
+    // same results, later.
     if (g > 0 && !c->gspare[g] && hipStreamCreateWithFlags(&c->gspare[g], hipStreamNonBlocking) != hipSuccess)
       return fail(TTSH_EHIP, "stream creation failed");
     if (!c->gstream[g] && hipStreamCreateWithFlags(&c->gstream[g], hipStreamNonBlocking) != hipSuccess)
