@@ -417,8 +417,8 @@ int ttsh_set_option(ttsh_ctx* ctx, int key, int64_t value);
 
 /* Unitary 2D DFT (Appendix C definition) of `batch` complex N x N arrays,
  * device pointers, interleaved float64 [batch][N][N][2]; inverse != 0 for the
- * iDFT.  precision 32 runs the library's FP32 transform (inputs rounded),
- * 64 the FP64 one.  Synchronous; in and out may alias.                      */
+ * iDFT.  precision 32 runs the library's FP32 transform (inputs rounded; sums
+ * of size up to 3e29), 64 the FP64 one.  Synchronous; in and out may alias. */
 int ttsh_fft2(const double* in, double* out, int N, int batch, int inverse, int precision);
 
 /* Streaming-bandwidth probe (measurement only; no part of the method): a

@@ -168,18 +168,25 @@ __device__ __forceinline__ C2<T> turn(C2<T> w) {  // tables hold the forward sig
   return DIR > 0 ? conj(w) : w;
 }
 
-// Entry j < N/2 of a factor table: e^{-2 pi i j / N} as (c, s/c), s/c taken
-// with the rounded c so that s = c (s/c) carries one rounding.  A quarter turn
-// has c = 0: 2^-30 (2^-60 in FP64) stands for it, at most 1/32 of the other
-// factors' rounding; a quarter turn of values above 3e29 (1e290) overflows.
+// The factor table of length N: entry j < N/2 is e^{-2 pi i j / N} as (c, s/c),
+// formed in long double, s/c with the rounded c so that s = c (s/c) carries one
+// rounding (with the angle and its functions in FP64 the FP64 transforms' error
+// is 1.2 to 1.5 times as large: 2.7e-16 against 1.8e-16 at 512 points).  A
+// quarter turn has c = 0: 2^-30 (2^-60 in FP64) stands for it, at most 1/32 of
+// the other factors' rounding; a quarter turn of values above 3e29 (1e290)
+// overflows.
 template <class T>
-C2<T> fft_factor(int j, int N) {
-  const double a = 2.0 * M_PI * (double)j / (double)N;
-  const T c = 4 * j == N ? std::ldexp((T)1, sizeof(T) == 8 ? -60 : -30) : (T)std::cos(a);
-  C2<T> w;
-  w.x = c;
-  w.y = (T)(-std::sin(a) / (double)c);
-  return w;
+void fft_factors(int N, C2<T>* w) {
+  for (int j = 0; j <= N / 4; ++j) {
+    const long double a = 2 * 3.14159265358979323846264338327950288L * j / N;
+    const T c = 4 * j == N ? std::ldexp((T)1, sizeof(T) == 8 ? -60 : -30) : (T)std::cos(a);
+    w[j].x = c;
+    w[j].y = (T)(-std::sin(a) / c);
+    if (j > 0 && 4 * j < N) {  // e^{-i (pi - a)}
+      w[N / 2 - j].x = -c;
+      w[N / 2 - j].y = -w[j].y;
+    }
+  }
 }
 
 // The four factors a thread's butterflies of one stage take: those of its one
@@ -301,7 +308,7 @@ __device__ __forceinline__ void lds_sync() {
 // ---- one Stockham stage, recursing into the next ---------------------------
 // v[f][e] holds element t + e*TT of transform f.  `lds` points at this group's
 // fft_slots(NF) regions of Padded<N> entries each.  tw: the table
-// of fft_factor(j, N), or its entries of every stage (Factors).
+// of fft_factors, or its entries of every stage (Factors).
 template <int N, int DIR, int NF, int P, class T, int SCH, bool WAVE, int S = 0>
 struct FftStage {
   static constexpr int E = kFftE;

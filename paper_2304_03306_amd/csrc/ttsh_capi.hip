@@ -276,11 +276,11 @@ void drop_graph(ttsh_ctx* c) {
   c->rem_steps = 0;
 }
 
-// the factor table of the transforms of length N (fft_factor)
+// the factor table of the transforms of length N on the device
 template <class T>
 int factor_table(int N, void** out) {
   std::vector<C2<T>> w(N / 2);
-  for (int j = 0; j < N / 2; ++j) w[j] = fft_factor<T>(j, N);
+  fft_factors(N, w.data());
   HIPCHK(hipMalloc(out, w.size() * sizeof(C2<T>)));
   HIPCHK(hipMemcpy(*out, w.data(), w.size() * sizeof(C2<T>), hipMemcpyHostToDevice));
   return TTSH_OK;

@@ -1,7 +1,8 @@
-// FP32 rounding error of the transforms of csrc/fft.hpp beside that of the
-// textbook stages (products with w^(r k), then the untwiddled DFT), against
-// FP64.  Prints per configuration: N, direction, schedule, RMS error and the
-// textbook's, both relative to the RMS output.
+// Rounding error of the transforms of csrc/fft.hpp beside that of the textbook
+// stages (products with w^(r k), then the untwiddled DFT) with factors rounded
+// once, against long double.  Prints per configuration: bits of the type, N,
+// direction, schedule, RMS error and the textbook's, both relative to the RMS
+// output.
 #include "lanes.hpp"
 
 #include <cstdio>
@@ -10,19 +11,43 @@
 #include "fft.hpp"
 
 using namespace ttsh;
+using X = long double;
+
+static C2<X> wave(X turn) {  // e^{-2 pi i turn}
+  const X a = 2 * 3.14159265358979323846264338327950288L * turn;
+  return mk(cosl(a), -sinl(a));
+}
 
 template <class T>
 static std::vector<C2<T>> waves(int N) {
   std::vector<C2<T>> w(N);
-  for (int j = 0; j < N; ++j) w[j] = mk((T)std::cos(2 * M_PI * j / N), (T)-std::sin(2 * M_PI * j / N));
+  for (int j = 0; j < N; ++j) w[j] = cvt<T>(wave((X)j / N));
   return w;
 }
 
 template <class T>
 static std::vector<C2<T>> table(int N) {
   std::vector<C2<T>> w(N / 2);
-  for (int j = 0; j < N / 2; ++j) w[j] = fft_factor<T>(j, N);
+  fft_factors(N, w.data());
   return w;
+}
+
+// the reference: halves of even and odd elements
+static std::vector<C2<X>> exact(const std::vector<C2<X>>& x, int dir) {
+  const int n = (int)x.size();
+  if (n == 1) return x;
+  std::vector<C2<X>> e(n / 2), o(n / 2), y(n);
+  for (int i = 0; i < n / 2; ++i) e[i] = x[2 * i], o[i] = x[2 * i + 1];
+  e = exact(e, dir);
+  o = exact(o, dir);
+  for (int i = 0; i < n / 2; ++i) {
+    C2<X> w = wave((X)i / n);
+    if (dir > 0) w = conj(w);
+    const C2<X> t = cmul(o[i], w);
+    y[i] = e[i] + t;
+    y[i + n / 2] = e[i] - t;
+  }
+  return y;
 }
 
 template <int N, int DIR, int SCH, class T, int P = 1>
@@ -44,56 +69,62 @@ void textbook(std::vector<C2<T>>& x, const std::vector<C2<T>>& w) {
   if constexpr (P * R < N) textbook<N, DIR, SCH, T, P * R>(x, w);
 }
 
-template <int N, int DIR, int SCH>
+template <class T, int N, int DIR, int SCH>
 void one() {
-  constexpr int TT = N / kFftE, COUNT = N <= 512 ? 32768 / N : 32;
-  const auto wf = waves<float>(N);
-  const auto wd = waves<double>(N);
-  const auto tf = table<float>(N);
+  constexpr int TT = N / kFftE, COUNT = N <= 1024 ? 16384 / N : 8;
+  const auto wt = waves<T>(N);
+  const auto ft = table<T>(N);
   std::mt19937_64 gen(N + DIR);
   std::normal_distribution<double> U(0, 1);
-  double ours = 0, book = 0, size = 0;
-  std::vector<C2<float>> lds(Padded<N, SCH>::value);
+  X ours = 0, book = 0, size = 0;
+  std::vector<C2<T>> lds(Padded<N, SCH>::value);
   for (int q = 0; q < COUNT; ++q) {
-    std::vector<C2<float>> x(N), y(N);
-    std::vector<C2<double>> d(N);
+    std::vector<C2<T>> x(N), y(N);
+    std::vector<C2<X>> d(N);
     for (int i = 0; i < N; ++i) {
-      x[i] = mk((float)U(gen), (float)U(gen));
-      d[i] = mk((double)x[i].x, (double)x[i].y);
+      x[i] = mk((T)U(gen), (T)U(gen));
+      d[i] = cvt<X>(x[i]);
     }
     lanes::run(TT, false, [&](int t) {
-      C2<float> v[1][kFftE];
+      C2<T> v[1][kFftE];
       for (int e = 0; e < kFftE; ++e) v[0][e] = x[t + e * TT];
-      fft<N, DIR, 1, SCH, false>(v, lds.data(), t, tf.data());
+      fft<N, DIR, 1, SCH, false>(v, lds.data(), t, ft.data());
       for (int e = 0; e < kFftE; ++e) y[t + e * TT] = v[0][e];
     });
-    textbook<N, DIR, SCH>(x, wf);
-    textbook<N, DIR, SCH>(d, wd);
+    textbook<N, DIR, SCH>(x, wt);
+    d = exact(d, DIR);
     for (int i = 0; i < N; ++i) {
-      ours += std::pow(y[i].x - d[i].x, 2) + std::pow(y[i].y - d[i].y, 2);
-      book += std::pow(x[i].x - d[i].x, 2) + std::pow(x[i].y - d[i].y, 2);
+      const C2<X> a = cvt<X>(y[i]) - d[i], b = cvt<X>(x[i]) - d[i];
+      ours += a.x * a.x + a.y * a.y;
+      book += b.x * b.x + b.y * b.y;
       size += d[i].x * d[i].x + d[i].y * d[i].y;
     }
   }
-  std::printf("%d %d %d %.4e %.4e\n", N, DIR, SCH, std::sqrt(ours / size), std::sqrt(book / size));
+  std::printf("%d %d %d %d %.4e %.4e\n", (int)sizeof(T) * 8, N, DIR, SCH, (double)sqrtl(ours / size),
+              (double)sqrtl(book / size));
 }
 
-template <int N>
+template <class T, int N>
 void both() {
-  one<N, -1, kSchedDefault>();
-  one<N, +1, kSchedDefault>();
+  one<T, N, -1, kSchedDefault>();
+  one<T, N, +1, kSchedDefault>();
+}
+template <class T>
+void all() {
+  both<T, 64>();
+  both<T, 128>();
+  both<T, 256>();
+  both<T, 512>();
+  both<T, 1024>();
+  both<T, 2048>();
+  both<T, 4096>();
+  both<T, 8192>();
+  one<T, 128, -1, sched_code(4, true)>();
+  one<T, 256, +1, sched_code(4, true)>();
 }
 
 int main() {
-  both<64>();
-  both<128>();
-  both<256>();
-  both<512>();
-  both<1024>();
-  both<2048>();
-  both<4096>();
-  both<8192>();
-  one<128, -1, sched_code(4, true)>();
-  one<256, +1, sched_code(4, true)>();
+  all<float>();
+  all<double>();
   return 0;
 }

@@ -21,7 +21,7 @@ static std::vector<C> table(int N) {
 
 static std::vector<C> factors(int N) {
   std::vector<C> w(N / 2);
-  for (int j = 0; j < N / 2; ++j) w[j] = fft_factor<double>(j, N);
+  fft_factors(N, w.data());
   return w;
 }
 
